@@ -113,10 +113,17 @@ int make_kparams(const dpd_params* p, KParams* k)
     // FP64 value (offsets below 4 cells); the band is ten times wider
     k->list_lo32 = (float)(k->rl2 * (1.0 - std::ldexp(1.0, -15)));
     k->list_hi32 = (float)(k->rl2 * (1.0 + std::ldexp(1.0, -15)));
-    // tile-frame positions reach 6 cell lengths from the frame origin: FP32
-    // separations are within ~2e-5 r_list^2 there; the band is ~6x wider
-    k->tile_lo32 = (float)(k->rl2 * (1.0 - std::ldexp(1.0, -13)));
-    k->tile_hi32 = (float)(k->rl2 * (1.0 + std::ldexp(1.0, -13)));
+    // The tile builder's units: 16 bits span 5.02 of the widest cells (cells
+    // of a stencil are less than 2 apart, so 3 (2 cells)^2 < 2^31).  A
+    // component of a separation is off by at most 1.02 units, two roundings of
+    // 0.5 and of FP32 frame positions below 6 cells (below 0.01 each), so a
+    // distance by at most 1.8 > sqrt(3) 1.02.
+    double widest = k->cell_len[0] > k->cell_len[1] ? k->cell_len[0] : k->cell_len[1];
+    widest = k->cell_len[2] > widest ? k->cell_len[2] : widest;
+    const double unit = 5.02 * widest / 65536.0, rq = r_list / unit;
+    k->tile_inv = (float)(1.0 / unit);
+    k->tile_lo = (uint32_t)std::floor((rq - 1.8) * (rq - 1.8));
+    k->tile_band = (uint32_t)std::ceil((rq + 1.8) * (rq + 1.8)) - k->tile_lo;
     k->rc2 = p->r_c * p->r_c;
     k->r_c = p->r_c;
     k->inv_rc = 1.0 / p->r_c;

@@ -41,8 +41,9 @@ struct KParams {
     int32_t small_dim[3]; // n_c < 4: a block's neighbourhood wraps onto itself
     int32_t nt[3];        // tiles of kTileX x kTileY x kTileZ cells per side (list builder)
     int32_t n_tiles;
-    float tile_lo32;      // FP32 pre-test of the tile builder (tile-frame positions):
-    float tile_hi32;      //   r^2 < lo is a neighbour, r^2 >= hi is not, else FP64 decides
+    float tile_inv;       // tile builder: positions in 16-bit units (length times tile_inv);
+    uint32_t tile_lo;     //   r^2 < tile_lo is a neighbour, r^2 >= tile_lo + tile_band is not,
+    uint32_t tile_band;   //   else FP64 decides
     float list_lo32;      // FP32 pre-test: r^2 < lo is a neighbour for sure,
     float list_hi32;      // r^2 >= hi is not; in between the FP64 test decides
     double rl2;           // (r_c + skin)^2, neighbour test  r^2 < rl2

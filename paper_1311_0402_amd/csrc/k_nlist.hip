@@ -433,22 +433,45 @@ void launch_nlist_pass(int waves, const KParams& kp, const BatchView& bv, int32_
 // One workgroup per tile of kTileX x kTileY x kTileZ cells (consecutive
 // Morton ranks, so the tile's particles are one index range).  The union of
 // its cells' stencils, (kTileX+2) x (kTileY+2) x (kTileZ+2) cells, is staged
-// in LDS: each union cell's particles in index order, as FP32 positions in
-// one tile frame (in-cell offset plus the cell's whole-cell offset from the
-// frame origin) with the particle index.  Each tile cell's 27 stencil cells
-// are put in ascending rank once, by one lane, with the same sorting
-// network, and stored as LDS ranges.  Each lane then walks its particle's
-// ranges in that order, one candidate per step, so its row comes out
-// ascending; the walk is one flat loop over all of the particle's
-// candidates, so lanes whose k-th stencil cells differ in size do not wait
-// for each other cell by cell.  Candidates come from LDS, so the walk issues
-// no global loads besides the row stores.  In a grid narrower than the
-// union (fewer than 10 x 6 x 6 cells) a cell can appear in the union at two
-// places, as two periodic images, and is staged twice; every tile cell's
-// 27 stencil cells are still distinct cells (3 or more per side), each at
-// the image next to it, so no candidate is seen twice.  Tiles whose
-// neighbourhood overflows the LDS take the lane builder's walk over global
-// memory.
+// in LDS: 16-bit positions and the particle indices, the cells in the order
+// of kUnionOrder, which puts most cells that follow each other in rank side
+// by side.  Each tile cell's 27 stencil cells are put in ascending rank once,
+// by one lane, with the same sorting network; those that follow each other
+// in LDS as well are joined, which leaves 10.5 runs of slots on average
+// instead of 27; the runs are cut into steps of four candidates, 27 on
+// average at density 3.  Each lane then walks its particle's steps in that
+// order, so its row comes out ascending.  A step with a hit leaves one 16-bit
+// word in LDS (first slot and four hit bits); the row is written from these
+// words afterwards, 16 bytes per store.
+//
+// Positions are counted in units of 1/13055 of the widest cell, 16 bits per
+// component modulo five cells (a candidate's cell touches the particle's, so
+// differences never wrap and squared distances stay below 2^31): four packed
+// integer instructions give the squared distance less the list radius's,
+// exact for the rounded positions, and its sign bit is the test.  Inside the
+// band that their rounding leaves open the FP64 rule decides (0.01 candidates
+// per particle at density 3).
+//
+// What bounds it: vector instructions.  A wave's instruction takes a SIMD four
+// clocks, and at 16M particles (density 3) ~2,600 of them per wave fill 88 %
+// of the time: the walk 40 % (8 instructions of distance test and 9 others
+// per four candidates), writing the rows 26 %, the sort and the runs 18 %.
+// Hence the wide steps, the joined runs and the integer test; a list of steps
+// rather than of runs keeps the walk free of run ends (30 instructions per
+// step fewer); rows leave two entries at a time since scattered stores cost
+// the texture address unit a clock per lane (one at a time 1,482 us at 16M and
+// 57 us at 262,144 particles of density 5, two 1,431 and 47, four 1,448 and
+// 49).  Measured, this kernel before and now: 16M particles 1,660 and 1,430 us;
+// 262,144 in a channel 51 and 46 us; 3,000 25 and 22 us.  Before, candidates
+// were tested in FP32 cell by cell, two per step, 60 steps a row, and each
+// stored or dropped by a scattered store of its own.
+//
+// In a grid narrower than the union (fewer than 10 x 6 x 6 cells) a cell can
+// appear in the union at two places, as two periodic images, and is staged
+// twice; every tile cell's 27 stencil cells are still distinct cells (3 or
+// more per side), each at the image next to it, so no candidate is seen
+// twice.  Tiles whose neighbourhood overflows the LDS take the lane
+// builder's walk over global memory.
 
 constexpr int kTUX = kTileX + 2, kTUY = kTileY + 2, kTUZ = kTileZ + 2;
 constexpr int kTU = kTUX * kTUY * kTUZ;          // union cells of a tile
@@ -462,19 +485,106 @@ template <int kW>
 constexpr int tile_pos() { return (kW * kWave * 29 / 10 + 15) / 16 * 16; }
 // union cell whose origin is the tile frame's origin (keeps |positions| small)
 constexpr int kTFX = kTileX / 2 + 1, kTFY = kTileY / 2 + 1, kTFZ = kTileZ / 2 + 1;
-// candidates a lane tests per step of the walk, and their operands
-constexpr int kStepW = 2;
-// a byte offset past the slab rows of every tile (a tile's rows span less
-// than INT32_MAX - 4 tile_pos bytes, or it is left to the lane builder)
-constexpr int32_t kDropOff = 0x7FFFFFF0;
-struct StepW {
-    float4 w[kStepW];
+// candidates a lane tests per step of the walk
+constexpr int kCand = 4;
+// steps of all tile cells together, each cell's followed by an empty one: the
+// staged slots' share of a stencil, and a step for each of 8 runs that end
+// inside one (a tile with more is left to the lane builder)
+template <int kW>
+constexpr int tile_steps() { return kTC * ((tile_pos<kW>() * 27 / kTU + kCand - 1) / kCand + 8); }
+static_assert(tile_pos<16>() < 4096, "12-bit LDS slots in the runs, the steps and the words");
+
+template <int kWords_, int kW>
+struct TileLds {
+    uint2 q[tile_pos<kW>() + kCand - 1];        // slots (see walk_pos); spare ones for reads past the end
+    int32_t gl[kTU];                            // a union cell's first particle less its first slot
+    uint32_t range[kTU];                        // its slots: start | end << 12
+    uint32_t cstep[kTC];                        // steps of a tile cell: first | number << 16
+    int32_t sum[2][kW];
+    uint8_t off[32];                            // a stencil cell's place among the union cells
+    alignas(16) uint16_t step[tile_steps<kW>()];            // first slot << 4 | four bits, the slots of the run
+    alignas(16) uint16_t word[kWords_ * kW * kWave];
 };
-// stencil entry: LDS start | LDS end << 12 | slab code << kSlabCodeShift
-// (the code is 0 when the slab is not coded), so an entry's code bits are
-// the ones a slab entry carries
-static_assert(tile_pos<16>() < 4096, "12-bit LDS offsets in the stencil entries");
-static_assert(kTC * 27 * 4 >= tile_pos<16>() * 2, "the staging map fits in the stencil table");
+// words a lane keeps before it writes its hits out: what the LDS leaves when
+// `groups` workgroups share a compute unit (rows have 14 words at most in 64
+// lanes at density 3, 30 at 8)
+template <int kW, int kGroups>
+constexpr int tile_words()
+{
+    constexpr int lds = 160 * 1024 / kGroups / 64 * 64;
+    constexpr int w = (lds - (int)sizeof(TileLds<0, kW>)) / (kW * kWave * 2);
+    return w < 32 ? w : 32;
+}
+
+// The union cells in their order in LDS: the 27 blocks of cells that lie in
+// one neighbouring tile each, the tile itself among them, and inside a block
+// by Morton code.  Cells of a block therefore ascend in rank (but for tiles
+// clipped at a high face, where fewer of them join).
+struct UnionOrder {
+    uint16_t u[kTU];
+};
+constexpr UnionOrder make_union_order()
+{
+    UnionOrder o{};
+    uint32_t key[kTU] = {};
+    for (int u = 0; u < kTU; ++u) {
+        const int c[3] = {u % kTUX, (u / kTUX) % kTUY, u / (kTUX * kTUY)};
+        const int side[3] = {kTileX, kTileY, kTileZ};
+        uint32_t k = 0;
+        for (int d = 0; d < 3; ++d) k = 3 * k + (c[d] == 0 ? 0 : c[d] == side[d] + 1 ? 2 : 1);
+        for (int b = 3; b >= 0; --b)
+            for (int d = 2; d >= 0; --d) k = 2 * k + (((c[d] + side[d] - 1) % side[d]) >> b & 1);
+        key[u] = k;
+    }
+    for (int u = 0; u < kTU; ++u) {
+        int at = 0;
+        for (int v = 0; v < kTU; ++v) at += key[v] < key[u] ? 1 : 0;
+        o.u[at] = (uint16_t)u;
+    }
+    return o;
+}
+__constant__ const UnionOrder kUnionOrder = make_union_order();
+
+// A slot: the particle's position in the walk's units, x | y << 16 and z, and
+// in the high half of the second word its union cell (9 bits) with the low
+// two bits of the cell's coordinates (6 bits, as in the slab's code).  A
+// particle that is not in its cell (a position that is no number, or outside
+// the box) has no neighbours: it stands 2.51 cells above its cell's middle,
+// more than 1.009 cells in z from whatever is compared with it (and so that
+// the squared distance stays below 2^31), and the top bit says so.
+typedef int16_t i16x2 __attribute__((ext_vector_type(2)));
+typedef int32_t i32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint2 walk_pos(const KParams& P, const float4& w, int32_t ux, int32_t uy, int32_t uz,
+                                          uint32_t cell)
+{
+    const float c0 = P.cell_len32[0], c1 = P.cell_len32[1], c2 = P.cell_len32[2], inv = P.tile_inv;
+    const float mx = 0.5f * c0, my = 0.5f * c1, mz = 0.5f * c2;
+    const bool in = fabsf(w.x - mx) <= 0.501f * c0 && fabsf(w.y - my) <= 0.501f * c1 &&
+                    fabsf(w.z - mz) <= 0.501f * c2;
+    const int32_t x = (int32_t)__builtin_rintf(((in ? w.x : mx) + (float)(ux - kTFX) * c0) * inv),
+                  y = (int32_t)__builtin_rintf(((in ? w.y : my) + (float)(uy - kTFY) * c1) * inv),
+                  z = (int32_t)__builtin_rintf(((in ? w.z : mz) + (float)(uz - kTFZ) * c2) * inv);
+    return make_uint2(((uint32_t)x & 0xFFFFu) | ((uint32_t)y << 16),
+                      (((uint32_t)z & 0xFFFFu) | cell << 16) ^ (in ? 0u : 0x80008000u));
+}
+
+// squared distance plus neg_lo
+__device__ __forceinline__ int32_t walk_test(const uint2& a, const uint2& b, int32_t neg_lo)
+{
+    const i16x2 xy = __builtin_bit_cast(i16x2, a.x) - __builtin_bit_cast(i16x2, b.x);
+    const int32_t z = (int16_t)(a.y - b.y);
+    return __builtin_amdgcn_sdot2(xy, xy, z * z + neg_lo, false);
+}
+
+__device__ __forceinline__ int32_t wave_max(int32_t v)
+{
+#pragma unroll 1
+    for (int d = kWave / 2; d > 0; d >>= 1) {
+        const int32_t o = __shfl_xor(v, d, kWave);
+        v = o > v ? o : v;
+    }
+    return __builtin_amdgcn_readfirstlane(v);
+}
 
 // exclusive prefix of v over the workgroup (kW waves); total gets the sum
 template <int kW>
@@ -532,7 +642,7 @@ __device__ __forceinline__ TileGeom tile_geom(const KParams& kp, const BatchView
     return g;
 }
 
-template <bool kB, int kW>
+template <bool kB, int kW, int kGroups>
 __global__ __launch_bounds__(kW * kWave) void k_nlist_tiles(KParams kp, BatchView bv, int32_t n_tiles, int32_t n,
                                                             const double* __restrict__ x,
                                                             const float* __restrict__ x32,
@@ -546,17 +656,20 @@ __global__ __launch_bounds__(kW * kWave) void k_nlist_tiles(KParams kp, BatchVie
 {
     if (gated_off(gate)) return;
     constexpr int kThreads = kW * kWave;
-    static_assert(kThreads >= kTU && kThreads >= kTC, "one thread per union cell and per tile cell");
-    __shared__ int32_t s_rank[kTU];
-    __shared__ int32_t s_gstart[kTU];
-    __shared__ int32_t s_lstart[kTU + 1];
-    constexpr int kTilePos = tile_pos<kW>();
-    __shared__ float4 s_pos[kTilePos + kStepW - 1];   // spare slots: a step's reads may run past the end
-    // (two spare entries: the walk reads up to two entries past a cell's last)
-    __shared__ uint32_t s_sten[kTC * 27 + 2];  // before the sort: union cell of every staged slot
-    __shared__ uint8_t s_nne[kTC];
-    __shared__ int32_t s_w[kW];
-    uint16_t* s_seg = reinterpret_cast<uint16_t*>(s_sten);
+    constexpr int kTilePos = tile_pos<kW>(), kSteps = tile_steps<kW>(), kWords = tile_words<kW, kGroups>();
+    static_assert(kThreads >= kTU && kThreads > kTC, "one thread per union cell, and waves to stage beside the cells'");
+    __shared__ TileLds<kWords, kW> lds;
+    // before the walk, in the words: each tile cell's runs (first slot | the
+    // cell's steps before it << 12 | length mod 4 << 30), their number before
+    // and an end after them; in the steps: ranks of the union cells and union
+    // cell of every slot
+    constexpr int kRuns = 29;
+    static_assert(kCand == 4, "a run's length mod 4 in two bits");
+    uint16_t* const s_seg = lds.step + 2 * kTU;
+    int32_t* const s_rank = reinterpret_cast<int32_t*>(lds.step);
+    uint32_t* const s_run = reinterpret_cast<uint32_t*>(lds.word);
+    static_assert(2 * kRuns * kTC <= kWords * kThreads, "the runs fit in the words");
+    static_assert(2 * kTU + kTilePos <= kSteps, "the ranks and the staging map fit in the steps");
 
     const int32_t tile = xcd_logical_id(blockIdx.x, gridDim.x);
     if (tile >= n_tiles) return;
@@ -567,10 +680,13 @@ __global__ __launch_bounds__(kW * kWave) void k_nlist_tiles(KParams kp, BatchVie
     // (the tile's slab rows are addressed with 32-bit byte offsets)
     const bool fits = (int64_t)(g.i_hi - g.i_lo) * slab_k * 4 + 4 * kTilePos < INT32_MAX;
 
-    // ---- union cells: thread u owns union cell u ----
-    int32_t cnt = 0;
+    if (tid < 27) lds.off[tid] = (uint8_t)(tid % 3 + kTUX * (tid / 3 % 3 + kTUY * (tid / 9)));
+
+    // ---- union cells: thread t owns the t-th in LDS ----
+    int32_t cnt = 0, u = 0;
     if (fits && tid < kTU) {
-        const int32_t ux = tid % kTUX, uy = (tid / kTUX) % kTUY, uz = tid / (kTUX * kTUY);
+        u = kUnionOrder.u[tid];
+        const int32_t ux = u % kTUX, uy = (u / kTUX) % kTUY, uz = u / (kTUX * kTUY);
         int32_t rank = INT_MAX, gs = 0;
         if (ux < g.v0 + 2 && uy < g.v1 + 2 && uz < g.v2 + 2) {
             rank = rank_tab[lin_cell(P, wrap_cell(g.o0 + ux - 1, P.nc[0]), wrap_cell(g.o1 + uy - 1, P.nc[1]),
@@ -578,84 +694,126 @@ __global__ __launch_bounds__(kW * kWave) void k_nlist_tiles(KParams kp, BatchVie
             gs = cell_start[rank];
             cnt = cell_start[rank + 1] - gs;
         }
-        s_rank[tid] = rank;
-        s_gstart[tid] = gs;
+        s_rank[u] = rank;
+        lds.gl[u] = gs;
     }
     int32_t total;
-    const int32_t ls = tile_excl_scan<kW>(cnt, s_w, total);
+    const int32_t ls = tile_excl_scan<kW>(cnt, lds.sum[0], total);
     if (!fits || total > kTilePos) {
         // left to the lane builder's walk over global memory (k_nlist_tile_rest)
         if (tid == 0) rest[1 + atomicAdd(rest, 1)] = tile;
         return;
     }
     if (tid < kTU) {
-        s_lstart[tid] = ls;
-        for (int32_t k = 0; k < cnt; ++k) s_seg[ls + k] = (uint16_t)tid;
-    }
-    if (tid == 0) s_lstart[kTU] = total;
-    __syncthreads();
-
-    // ---- staging: every union particle in the tile frame ----
-    const float4* __restrict__ xw = reinterpret_cast<const float4*>(x32);
-    const float cl0 = P.cell_len32[0], cl1 = P.cell_len32[1], cl2 = P.cell_len32[2];
-    for (int32_t p = tid; p < total; p += kThreads) {
-        const int32_t u = s_seg[p];
-        const int32_t j = s_gstart[u] + (p - s_lstart[u]);
-        const float4 w = xw[j];
-        const int32_t ux = u % kTUX, uy = (u / kTUX) % kTUY, uz = u / (kTUX * kTUY);
-        s_pos[p] = make_float4(w.x + (float)(ux - kTFX) * cl0, w.y + (float)(uy - kTFY) * cl1,
-                               w.z + (float)(uz - kTFZ) * cl2, __int_as_float(j));
+        lds.gl[u] -= ls;
+        lds.range[u] = (uint32_t)ls | (uint32_t)(ls + cnt) << 12;
+        for (int32_t k = 0; k < cnt; ++k) s_seg[ls + k] = (uint16_t)u;
     }
     __syncthreads();
 
-    // ---- each tile cell's non-empty stencil cells in ascending rank ----
-    if (tid < kTC) {
-        const int32_t lx = tid % kTileX, ly = (tid / kTileX) % kTileY, lz = tid / (kTileX * kTileY);
-        if (lx < g.v0 && ly < g.v1 && lz < g.v2) {
-            uint32_t key[27];
+    // ---- staging: every union particle in the tile frame, by the waves that
+    // have no cells below ----
+    if (tid >= kTC) {
+        constexpr int kStagers = kThreads - kTC, kRounds = (kTilePos + kStagers - 1) / kStagers;
+        const float4* __restrict__ xw = reinterpret_cast<const float4*>(x32);
+        // (all rounds' records requested before the first is converted)
+        float4 w[kRounds];
+        int32_t cell[kRounds];
 #pragma unroll
-            for (int c = 0; c < 27; ++c) {
-                const int32_t u = (lx + c % 3) + kTUX * ((ly + (c / 3) % 3) + kTUY * (lz + c / 9));
-                key[c] = ((uint32_t)s_rank[u] << 5) | (uint32_t)c;
+        for (int q = 0; q < kRounds; ++q) {
+            const int32_t p = tid - kTC + q * kStagers;
+            cell[q] = 0;
+            if (p < total) {
+                cell[q] = s_seg[p];
+                w[q] = xw[lds.gl[cell[q]] + p];
             }
+        }
 #pragma unroll
-            for (int c = 0; c < kNet27.count; ++c) {
-                const uint32_t a = key[kNet27.a[c]], b = key[kNet27.b[c]];
-                key[kNet27.a[c]] = a < b ? a : b;
-                key[kNet27.b[c]] = a < b ? b : a;
-            }
-            uint32_t* st = s_sten + tid * 27;
-            const uint32_t cmask = n <= kSlabJMask ? ~0u : 0u;     // uncoded slab: no code bits
-            int32_t m = 0;
-#pragma unroll
-            for (int q = 0; q < 27; ++q) {
-                const int32_t c = (int32_t)(key[q] & 31u);
-                const int32_t ex = c % 3, ey = (c / 3) % 3, ez = c / 9;
-                const int32_t u = (lx + ex) + kTUX * ((ly + ey) + kTUY * (lz + ez));
-                const uint32_t code = ((uint32_t)ex | ((uint32_t)ey << 2) | ((uint32_t)ez << 4)) & cmask;
-                const int32_t a = s_lstart[u], b = s_lstart[u + 1];
-                if (a < b) st[m++] = (uint32_t)a | ((uint32_t)b << 12) | (code << kSlabCodeShift);
-            }
-            s_nne[tid] = (uint8_t)m;
-            // the walk reads up to two entries past a cell's last: empty
-            // ranges at slot 0
-            for (int32_t q = m; q < 27; ++q) st[q] = 0u;
-        } else {
-            for (int32_t q = 0; q < 27; ++q) s_sten[tid * 27 + q] = 0u;
+        for (int q = 0; q < kRounds; ++q) {
+            const int32_t p = tid - kTC + q * kStagers, c = cell[q];
+            const int32_t ux = c % kTUX, uy = (c / kTUX) % kTUY, uz = c / (kTUX * kTUY);
+            const uint32_t code = (uint32_t)(ux & 3) | (uint32_t)(uy & 3) << 2 | (uint32_t)(uz & 3) << 4;
+            if (p < total)
+                lds.q[p] = walk_pos(P, w[q], ux, uy, uz, (uint32_t)c | code << 9);
         }
     }
-    if (tid < 2) s_sten[kTC * 27 + tid] = 0u;
+
+    // ---- each tile cell's runs: its non-empty stencil cells in ascending rank ----
+    const bool is_cell = tid < kTC && tid % kTileX < g.v0 && (tid / kTileX) % kTileY < g.v1 &&
+                         tid / (kTileX * kTileY) < g.v2;
+    uint32_t key[27];
+    uint32_t* const run = s_run + tid * kRuns;
+    int32_t m = 0, n_run = 0;
+    if (is_cell) {
+        const int32_t u0 = tid % kTileX + kTUX * ((tid / kTileX) % kTileY + kTUY * (tid / (kTileX * kTileY)));
+#pragma unroll
+        for (int c = 0; c < 27; ++c)
+            key[c] = ((uint32_t)s_rank[u0 + c % 3 + kTUX * ((c / 3) % 3 + kTUY * (c / 9))] << 5) | (uint32_t)c;
+#pragma unroll
+        for (int c = 0; c < kNet27.count; ++c) {
+            const uint32_t a = key[kNet27.a[c]], b = key[kNet27.b[c]];
+            key[kNet27.a[c]] = a < b ? a : b;
+            key[kNet27.b[c]] = a < b ? b : a;
+        }
+#pragma unroll
+        for (int q = 0; q < 27; ++q) key[q] = lds.range[u0 + lds.off[key[q] & 31u]];
+        // Joined and counted without branches: a joined cell writes its run
+        // again, with the new end, an empty one as it was; before the first
+        // run stands one from 0 to ~0, which counts as no steps.
+        uint32_t start = 0, end = ~0u;
+#pragma unroll
+        for (int q = 0; q < 27; ++q) {
+            const uint32_t a = key[q] & 0xFFFu, b = key[q] >> 12;
+            const bool some = a < b, turn = some && a != end;
+            m += turn ? (int32_t)((end - start + kCand - 1) / kCand) : 0;
+            start = turn ? a : start;
+            n_run += turn ? 1 : 0;
+            end = some ? b : end;
+            run[n_run] = start | (uint32_t)m << 12 | (end - start) << 30;
+        }
+        m += (int32_t)((end - start + kCand - 1) / kCand);
+        run[0] = (uint32_t)n_run;
+        run[n_run + 1] = (uint32_t)m << 12;
+        m += 1;                                                      // (the empty step)
+    }
+    int32_t n_steps;
+    const int32_t at_step = tile_excl_scan<kW>(m, lds.sum[1], n_steps);
+    if (n_steps > kSteps) {
+        if (tid == 0) rest[1 + atomicAdd(rest, 1)] = tile;
+        return;
+    }
+    if (is_cell) {
+        lds.cstep[tid] = (uint32_t)at_step | (uint32_t)m << 16;
+        lds.step[at_step + m - 1] = 0;
+    } else if (tid < kTC) {
+        run[0] = 0;
+    }
+    __syncthreads();
+
+    // ---- the runs' steps: kPer lanes share a cell's runs ----
+    constexpr int kPer = kThreads / kTC;
+    if (tid < kPer * kTC) {
+        const uint32_t* const cr = s_run + tid % kTC * kRuns;
+        const int32_t nr = (int32_t)cr[0];
+#pragma unroll 1
+        for (int32_t r = 1 + tid / kTC; r <= nr; r += kPer) {
+            const uint32_t w = cr[r], first = w >> 12 & 0x3FFFFu, rem = w >> 30;
+            int32_t steps = (int32_t)((cr[r + 1] >> 12 & 0x3FFFFu) - first);
+            uint16_t* st = lds.step + (lds.cstep[tid % kTC] & 0xFFFFu) + first;
+            uint32_t word = w << kCand | 15u;
+            for (; steps > 1; --steps, word += kCand << kCand) *st++ = (uint16_t)word;
+            *st = (uint16_t)(rem ? word & ~15u | ((1u << rem) - 1u) : word);
+        }
+    }
     __syncthreads();
 
     // ---- the walk: one lane per particle of the tile ----
-    // kStepW candidates of a cell per step (slots k, k + 1, ...; slots past
-    // the cell's end idle, and their reads may be the spare slots past the
-    // staged range, never used).  The next step's candidates and the stencil
-    // entry after the next are requested from LDS before the current ones
-    // are tested; two steps per loop turn alternate the buffers.
-    const float lo = P.tile_lo32, hi = P.tile_hi32;
+    // The next step's candidates and the step after the next are requested
+    // from LDS before the current ones are tested.  A lane that has ended
+    // stays on its empty step.
+    const int32_t neg_lo = -(int32_t)P.tile_lo;
+    const uint32_t band = P.tile_band;
     const int64_t N = n;
-    constexpr uint32_t kCodeBits = ~0u << kSlabCodeShift;
     // The tile's slab rows through a buffer resource: a row longer than the
     // slab width runs on into the next rows of the tile (stores past the
     // tile's last row are dropped by the range check); such a row sets the
@@ -663,83 +821,114 @@ __global__ __launch_bounds__(kW * kWave) void k_nlist_tiles(KParams kp, BatchVie
     const int32_t n_here = g.i_hi - g.i_lo;
     const auto rows = __builtin_amdgcn_make_buffer_rsrc(slab + (int64_t)g.i_lo * slab_k, (short)0,
                                                         n_here * slab_k * (int32_t)sizeof(int32_t), 0x00020000);
+    const uint32_t code_bits = n <= kSlabJMask ? ~0u << kSlabCodeShift : 0u;      // none: uncoded slab
+    // A hit's entry is its particle with the code the difference of the cell
+    // coordinates plus one, each two bits wide: a subtraction without borrows
+    // between them (the code's high bits set before and put right after).
+    const uint32_t hbit = 0xA8000000u & code_bits;
+    static_assert(0x2Au << kSlabCodeShift == 0xA8000000u && kSlabCodeShift == 26, "the code's high bits");
+    uint16_t* const list = lds.word + tid;
     for (int32_t i = g.i_lo + tid; i < g.i_hi; i += kThreads) {
         const uint32_t me = cell_xyz[i];
         const int32_t lx = (int32_t)(me & 1023u) - g.o0, ly = (int32_t)((me >> 10) & 1023u) - g.o1,
                       lz = (int32_t)(me >> 20) - g.o2;
-        const int32_t ui = (lx + 1) + kTUX * ((ly + 1) + kTUY * (lz + 1));
-        const float4 wi = s_pos[s_lstart[ui] + (i - s_gstart[ui])];
-        const int32_t ci = lx + kTileX * (ly + kTileY * lz);
-        const uint32_t* st = s_sten + ci * 27;
-        const int32_t nne = s_nne[ci];                   // >= 1: i's own cell is in its stencil
-        // byte offset of this lane's next entry in the tile's slab rows
+        const int32_t self = i - lds.gl[(lx + 1) + kTUX * ((ly + 1) + kTUY * (lz + 1))];
+        const uint2 qi = lds.q[self];
+        const uint32_t cs = lds.cstep[lx + kTileX * (ly + kTileY * lz)];
+        // (none for a particle that is not in its cell, else one or more: i's
+        // own cell is in its stencil)
+        const uint16_t* const p_end = lds.step + (cs & 0xFFFFu) + (cs >> 16) - 1u;
+        const int32_t n_st = qi.y >> 31 ? 0 : (int32_t)(cs >> 16) - 1;
+        const uint16_t* p = p_end - n_st;
+        int32_t left = wave_max(n_st);
+        const uint32_t own = (uint32_t)(lx & 3) << 26 | (uint32_t)(ly & 3) << 28 | (uint32_t)(lz & 3) << 30;
+        const uint32_t own_lo = own & code_bits & ~hbit, own_hi = ~own & hbit;
         const int32_t row0 = (i - g.i_lo) * slab_k * (int32_t)sizeof(int32_t);
-        int32_t rb = row0;
-        // walk state: the current stencil entry cur (its cell's slots end at
-        // bits 12..23, its slab code in the top bits), the candidate slot k,
-        // and the entry after cur (ent_n, at index pn)
-        uint32_t cur = st[0];
-        int32_t pn = 1;
-        uint32_t ent_n = st[1];
-        int32_t k = (int32_t)(cur & 0xFFFu);
-        // the FP32 test of one candidate: hit (inside lo) or band (between
-        // lo and hi, to be decided by the FP64 rule)
-        auto pre = [&](const float4& w, bool valid, bool& band) {
-            const float dx = wi.x - w.x, dy = wi.y - w.y, dz = wi.z - w.z;
-            const float r2 = __fmaf_rn(dz, dz, __fmaf_rn(dy, dy, dx * dx));
-            const bool near = r2 < lo;
-            band = valid && !near && r2 < hi;
-            // i itself has r2 = 0 < lo, so the band never holds it
-            return valid && near && __float_as_int(w.w) != i;
+        int32_t rb = row0;                                // byte offset of the row's next entry
+        uint32_t last = 0;                                // the one before, stored with the next in one store
+        int32_t at = 0;
+        auto next_step = [&] {
+            p = p + 1 < p_end ? p + 1 : p_end;
+            return (uint32_t)*p;
         };
-        auto store = [&](const float4& w, uint32_t ent, bool hit) {
-            // every lane stores: a miss at an offset past the rows' range,
-            // which the buffer's range check drops (no branch per candidate)
-            __builtin_amdgcn_raw_buffer_store_b32((int32_t)((ent & kCodeBits) | (uint32_t)__float_as_int(w.w)),
-                                                  rows, hit ? rb : kDropOff, 0, 0);
-            rb += hit ? (int32_t)sizeof(int32_t) : 0;
+        auto request = [&](uint32_t st, uint2 (&w)[kCand]) {
+            const uint2* q = lds.q + (st >> kCand);
+#pragma unroll
+            for (int c = 0; c < kCand; ++c) w[c] = q[c];
         };
-        // one step on the candidates at slots k .. k + kStepW - 1 (those below
-        // the cell's end), advancing the state and requesting the next step's
-        // candidates into nxt and the entry after the next; false when the
-        // walk has ended.  Past the end the state runs on into the following
-        // entries of the table (the next cell's, or the zeroed ones), whose
-        // slots are valid reads and never tested.
-        auto step = [&](const StepW& cw, StepW& nxt) {
-            const uint32_t ent = cur;
-            const int32_t left = (int32_t)((ent >> 12) & 0xFFFu) - k;   // >= 1
-            const bool adv = left <= kStepW;
-            k = adv ? (int32_t)(ent_n & 0xFFFu) : k + kStepW;
-            cur = adv ? ent_n : cur;
-            pn += adv ? 1 : 0;
-            const float4* p = s_pos + k;
+        // step st on the candidates w; the next step's are requested first
+        auto step = [&](uint32_t& st, uint32_t st_n, const uint2 (&w)[kCand], uint2 (&w_n)[kCand]) {
+            const uint32_t now = st;
+            request(st_n, w_n);
+            st = next_step();
+            int32_t t[kCand];
+            uint32_t hits = 0, open = ~0u;
 #pragma unroll
-            for (int m = 0; m < kStepW; ++m) nxt.w[m] = p[m];
-            ent_n = st[pn];
-            bool hit[kStepW], band[kStepW];
-            bool any_band = false;
-#pragma unroll
-            for (int m = 0; m < kStepW; ++m) {
-                hit[m] = pre(cw.w[m], m == 0 || m < left, band[m]);
-                any_band = any_band || band[m];
+            for (int c = kCand - 1; c >= 0; --c) {
+                t[c] = walk_test(qi, w[c], neg_lo);
+                hits = __builtin_amdgcn_alignbit(hits, (uint32_t)t[c], 31);      // hits << 1 | t < 0
+                open = min(open, (uint32_t)t[c]);                 // below `band`: the FP64 rule decides
             }
-            // the band is rare: the wave branches once per step on its ballot
-            if (__builtin_expect(__ballot(any_band) != 0ull, 0)) {
-#pragma unroll
-                for (int m = 0; m < kStepW; ++m)
-                    if (band[m]) hit[m] = exact_hit(P, x, N, i, __float_as_int(cw.w[m].w));
+            // rare: the wave branches on the ballot
+            if (__builtin_expect(__ballot(open < band) != 0ull, 0)) {
+#pragma unroll 1
+                for (int c = 0; c < kCand; ++c) {
+                    const int32_t q = c == 0 ? t[0] : c == 1 ? t[1] : c == 2 ? t[2] : t[3];
+                    if ((now >> c & 1u) && (uint32_t)q < band) {
+                        const int32_t sl = (int32_t)(now >> kCand) + c;
+                        const int32_t j = lds.gl[lds.q[sl].y >> 16 & 511u] + sl;
+                        if (exact_hit(P, x, N, i, j)) hits |= 1u << c;
+                    }
+                }
             }
-#pragma unroll
-            for (int m = 0; m < kStepW; ++m) store(cw.w[m], ent, hit[m]);
-            return pn <= nne;
+            // written at the list's end, which moves past it if it holds a hit
+            hits &= now;
+            list[at] = (uint16_t)((now & ~15u) | hits);
+            at += hits ? kThreads : 0;
         };
-        StepW s0, s1;
-#pragma unroll
-        for (int m = 0; m < kStepW; ++m) s0.w[m] = s_pos[k + m];
-        for (;;) {
-            if (!step(s0, s1)) break;
-            if (!step(s1, s0)) break;
+        uint32_t sa = *p, sb = next_step();
+        uint2 wa[kCand], wb[kCand];
+        request(sa, wa);
+        while (left > 0) {
+            do {
+                step(sa, sb, wa, wb);
+                step(sb, sa, wb, wa);
+                left -= 2;
+            } while (left > 0 && __ballot(at > (kWords - 4) * kThreads) == 0ull);
+            // The words' hits, lowest bit first.  Reads run ahead: the word
+            // after the current one, and a hit's union cell, used a turn later
+            // (the particle itself stands for no hit).
+            int32_t gp = 0, sl_p = self;
+            uint32_t word = list[0], word_n = list[kThreads], cell_p = 0;
+            for (bool more = true; more;) {
+                more = __ballot(gp < at) != 0ull;
+                int32_t sl = self;
+                uint32_t cell = 0;
+                if (gp < at) {
+                    sl = (int32_t)(word >> kCand) + __builtin_ctz(word);
+                    cell = lds.q[sl].y;
+                    word &= word - 1u;                    // (its lowest set bit: one of the four)
+                    const bool turn = (word & 15u) == 0u;
+                    word = turn ? word_n : word;
+                    gp += turn ? kThreads : 0;
+                    word_n = list[gp + kThreads];
+                }
+                if (sl_p != self) {
+                    const uint32_t e = (uint32_t)(lds.gl[cell_p >> 16 & 511u] + sl_p) | (cell_p << 1 & code_bits);
+                    const uint32_t entry = ((e | hbit) - own_lo) ^ ((e ^ own_hi) & hbit);
+                    rb += (int32_t)sizeof(int32_t);
+                    if ((rb & 4) == 0) {
+                        const i32x2 v = {(int32_t)last, (int32_t)entry};
+                        __builtin_amdgcn_raw_buffer_store_b64(v, rows, rb - 8, 0, 0);
+                    }
+                    last = entry;
+                }
+                sl_p = sl;
+                cell_p = cell;
+            }
+            at = 0;
         }
+        if (rb & 4) __builtin_amdgcn_raw_buffer_store_b32((int32_t)last, rows, rb - 4, 0, 0);
         const int32_t row = (rb - row0) / (int32_t)sizeof(int32_t);
         offset[i] = row;
         if (row > slab_k) atomicOr(flag, 1);
@@ -771,13 +960,13 @@ __global__ __launch_bounds__(kBlock) void k_nlist_tile_rest(KParams kp, BatchVie
     }
 }
 
-template <bool kB, int kW>
+template <bool kB, int kW, int kGroups>
 void launch_nlist_tiles_t(const KParams& kp, const BatchView& bv, int32_t n_tiles, int32_t n, const double* x,
                           const float* x32, const uint32_t* cell_xyz, const int32_t* cell_start,
                           const int32_t* rank_tab, int32_t* offset, int32_t* slab, int32_t slab_k, int32_t* flag,
                           int32_t* rest, hipStream_t s, Gate gate)
 {
-    hipLaunchKernelGGL((k_nlist_tiles<kB, kW>), dim3(n_tiles), dim3(kW * kWave), 0, s, kp, bv, n_tiles, n, x, x32,
+    hipLaunchKernelGGL((k_nlist_tiles<kB, kW, kGroups>), dim3(n_tiles), dim3(kW * kWave), 0, s, kp, bv, n_tiles, n, x, x32,
                        cell_xyz, cell_start, rank_tab, offset, slab, slab_k, flag, rest, gate);
 }
 
@@ -788,15 +977,21 @@ void launch_nlist_tiles(int waves, const KParams& kp, const BatchView& bv, int32
                         const int32_t* rank_tab, int32_t* offset, int32_t* slab, int32_t slab_k, int32_t* flag,
                         int32_t* rest, hipStream_t s, Gate gate)
 {
-#define DPD_TILE_CASE(W)                                                                                         \
-    launch_nlist_tiles_t<kB, W>(kp, bv, n_tiles, n, x, x32, cell_xyz, cell_start, rank_tab, offset, slab, slab_k, \
-                                flag, rest, s, gate)
-    if (waves <= 6) DPD_TILE_CASE(6);
-    else if (waves <= 7) DPD_TILE_CASE(7);
-    else if (waves <= 8) DPD_TILE_CASE(8);
-    else if (waves <= 10) DPD_TILE_CASE(10);
-    else if (waves <= 12) DPD_TILE_CASE(12);
-    else DPD_TILE_CASE(16);
+    // Workgroups sharing a compute unit: as many as its 32 waves allow, but
+    // one of 16 waves, with 32 words a lane against 18, where each of the 256
+    // units gets two tiles at most (10 systems of 4,608 particles, 180 tiles:
+    // 46.6 and 54.4 us; 1M particles at r_c + skin, 1,200 tiles: 85 and 84 us,
+    // and 16 us more per build in a long run).
+#define DPD_TILE_CASE(W, G)                                                                                      \
+    launch_nlist_tiles_t<kB, W, G>(kp, bv, n_tiles, n, x, x32, cell_xyz, cell_start, rank_tab, offset, slab,      \
+                                   slab_k, flag, rest, s, gate)
+    if (waves <= 6) DPD_TILE_CASE(6, 4);
+    else if (waves <= 7) DPD_TILE_CASE(7, 4);
+    else if (waves <= 8) DPD_TILE_CASE(8, 3);
+    else if (waves <= 10) DPD_TILE_CASE(10, 3);
+    else if (waves <= 12) DPD_TILE_CASE(12, 2);
+    else if (n_tiles > 512) DPD_TILE_CASE(16, 2);
+    else DPD_TILE_CASE(16, 1);
 #undef DPD_TILE_CASE
     const int grid = n_tiles < 1024 ? n_tiles : 1024;
     hipLaunchKernelGGL((k_nlist_tile_rest<kB>), dim3(grid), dim3(kBlock), 0, s, kp, bv, n, x, x32, cell_xyz,
