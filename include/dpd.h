@@ -441,8 +441,8 @@ int dpd_tea_gaussians(int64_t n, const uint32_t* sig_i, const uint32_t* sig_j, u
 
 /* Throughput probe: every thread t < n_tags draws the Gaussians of pairs
  * (t, t + 1), ..., (t, t + pairs_per_thread) (tags mod n_tags) and writes
- * their sum to sink[t].  generator 0: Philox4x32-10 and the device
- * library's log, sqrt and cospi (the FP64 force pass's generator);
+ * their sum to sink[t].  generator 0: Philox4x32-10 and the FP64
+ * force pass's Box-Muller;
  * generator 1: TEA-4 on sig[] (from dpd_tea_signatures) with the fast
  * logarithm and cosine.  pairs_per_thread < n_tags (else DPD_EINVAL). */
 int dpd_gaussian_throughput(int32_t generator, int32_t n_tags, int32_t pairs_per_thread, uint64_t step,

@@ -80,6 +80,7 @@ int make_kparams(const dpd_params* p, KParams* k)
                         d, p->box[d], r_list);
         k->L[d] = p->box[d];
         k->halfL[d] = 0.5 * p->box[d];
+        k->inv_L[d] = 1.0 / p->box[d];
         k->inv_cell[d] = (double)k->nc[d] / p->box[d];
         k->cell_len[d] = p->box[d] / (double)k->nc[d];
         k->cell_len32[d] = (float)k->cell_len[d];

@@ -28,6 +28,7 @@ constexpr int kTileX = 8, kTileY = 4, kTileZ = 4;
 struct KParams {
     double L[3];          // box
     double halfL[3];      // L / 2 (exact)
+    double inv_L[3];      // 1 / L
     double inv_cell[3];   // n_c / L  (cell coordinate = trunc(x * inv_cell))
     double cell_len[3];   // L / n_c  (origin of a cell, mixed-precision offsets)
     float cell_len32[3];
@@ -289,12 +290,103 @@ __device__ __forceinline__ U4 pair_words(uint32_t ti, uint32_t tj, uint64_t step
     return philox4x32_10(U4{a, b, (uint32_t)step, (uint32_t)(step >> 32)}, seed_lo, seed_hi);
 }
 
+// Square root and its reciprocal of q > 0 (not subnormal): the hardware
+// estimate (relative error 2^-22 or less), one third-order step from the
+// residual 1 - q y^2, and for the root a residual more (within an ulp of the
+// rounded values; 16 instructions for both where the library's root and
+// division take 40).
+struct RootPair {
+    double root, inv;
+};
+
+__device__ __forceinline__ RootPair root_pair(double q)
+{
+    const double y = __builtin_amdgcn_rsq(q);
+    const double g = q * y;
+    const double e = __fma_rn(-g, y, 1.0);
+    const double t = e * __fma_rn(e, 0.375, 0.5);
+    RootPair o;
+    o.inv = __fma_rn(y, t, y);
+    const double r = __fma_rn(g, t, g);
+    o.root = __fma_rn(__fma_rn(-r, r, q), 0.5 * o.inv, r);
+    return o;
+}
+
+// distance from its square: 0 has no reciprocal (a direction from it is no number)
+__device__ __forceinline__ RootPair distance(double r2)
+{
+    RootPair o = root_pair(r2);
+    o.root = r2 > 0.0 ? o.root : r2;
+    return o;
+}
+
+// -2 ln u, u = (w + 1/2) 2^-32: u = m 2^e with m in [sqrt(1/2), sqrt(2)),
+// ln m = 2 atanh(s), s = (m - 1) / (m + 1), |s| < 0.172, by its series to
+// s^21 (remainder below 2^-57 of the sum); ln 2 in two parts, the first of 41
+// bits, so that its multiple is exact.  A 32-bit uniform needs none of the
+// library's special cases.
+__device__ __forceinline__ double neg2_ln_u32(uint32_t w)
+{
+    const double x = (double)w + 0.5;
+    double m = __builtin_amdgcn_frexp_mant(x);                  // [1/2, 1)
+    const bool low = m < 0.70710678118654752;
+    const double e = (double)(__builtin_amdgcn_frexp_exp(x) - (low ? 33 : 32));
+    m = low ? m + m : m;
+    const double n = m - 1.0, d = m + 1.0;
+    const double y0 = __builtin_amdgcn_rcp(d);
+    const double e0 = __fma_rn(-d, y0, 1.0);
+    const double y = __fma_rn(y0, __fma_rn(e0, e0, e0), y0);
+    double s = n * y;
+    s = __fma_rn(__fma_rn(-s, d, n), y, s);
+    const double z = s * s;
+    double p = -4.0 / 21.0;
+    p = __fma_rn(p, z, -4.0 / 19.0);
+    p = __fma_rn(p, z, -4.0 / 17.0);
+    p = __fma_rn(p, z, -4.0 / 15.0);
+    p = __fma_rn(p, z, -4.0 / 13.0);
+    p = __fma_rn(p, z, -4.0 / 11.0);
+    p = __fma_rn(p, z, -4.0 / 9.0);
+    p = __fma_rn(p, z, -4.0 / 7.0);
+    p = __fma_rn(p, z, -4.0 / 5.0);
+    p = __fma_rn(p, z, -4.0 / 3.0);
+    const double lo = __fma_rn(s * z, p, e * 0x1.8432a1b0e2634p-42);
+    return __fma_rn(e, -0x1.62e42fefa4p+0, __fma_rn(-4.0, s, lo));
+}
+
+// cos(2 pi u), u = w 2^-32: the nearest quarter turn q and the rest x in
+// [-1/2, 1/2] quarters, exactly, in integers; sin and cos of pi/2 x by their
+// series to x^17 and x^16 (remainders 8e-20 and 2e-18), the leading
+// coefficients in two parts (within an ulp of the rounded value).
+__device__ __forceinline__ double cos_turn_u32(uint32_t w)
+{
+    const uint32_t q = w + 0x20000000u;
+    const double x = (double)(int32_t)((q & 0x3FFFFFFFu) - 0x20000000u) * 0x1p-30;
+    const double z = x * x;
+    double sn = 0x1.aaec32af93359p-38;
+    sn = __fma_rn(sn, z, -0x1.6fadb9f155744p-31);
+    sn = __fma_rn(sn, z, 0x1.e8f434d018d63p-25);
+    sn = __fma_rn(sn, z, -0x1.e3074fde8871fp-19);
+    sn = __fma_rn(sn, z, 0x1.50783487ee782p-13);
+    sn = __fma_rn(sn, z, -0x1.32d2cce62bd86p-8);
+    sn = __fma_rn(sn, z, 0x1.466bc6775aae2p-4);
+    sn = __fma_rn(sn, z, -0x1.4abbce625be53p-1);
+    sn = __fma_rn(x, 0x1.921fb54442d18p+0, x * __fma_rn(sn, z, 0x1.1a62633145c07p-54));
+    double cs = 0x1.20c62c2f2d7f5p-34;
+    cs = __fma_rn(cs, z, -0x1.b6e24f44b128fp-28);
+    cs = __fma_rn(cs, z, 0x1.f9d38a3763cc3p-22);
+    cs = __fma_rn(cs, z, -0x1.a6d1f2a204a8cp-16);
+    cs = __fma_rn(cs, z, 0x1.e1f506891babbp-11);
+    cs = __fma_rn(cs, z, -0x1.55d3c7e3cbffap-6);
+    cs = __fma_rn(cs, z, 0x1.03c1f081b5ac4p-2);
+    cs = 1.0 + __fma_rn(z, -0x1.3bd3cc9be45dep+0, z * __fma_rn(cs, z, -0x1.692b71366cc04p-54));
+    const double r = q & 0x40000000u ? sn : cs;
+    return __longlong_as_double(__double_as_longlong(r) ^ ((long long)((q + 0x40000000u) & 0x80000000u) << 32));
+}
+
 // xi = sqrt(-2 ln u1) cos(2 pi u2), u1 = (w0 + 1/2) 2^-32, u2 = w1 2^-32 (FP64)
 __device__ __forceinline__ double gauss64(U4 w)
 {
-    const double u1 = ((double)w.x + 0.5) * 0x1p-32;
-    const double u2 = (double)w.y * 0x1p-32;
-    return sqrt(-2.0 * log(u1)) * cospi(2.0 * u2);
+    return root_pair(neg2_ln_u32(w.x)).root * cos_turn_u32(w.y);
 }
 
 // Same variate in FP32 with the hardware transcendentals: v_log_f32 (log2),

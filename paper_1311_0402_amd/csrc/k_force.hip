@@ -166,12 +166,12 @@ __device__ __forceinline__ void add_bonds_body(const KParams& kp, const ForceArg
             const double dx = min_image(xi - a.x[j], kp.L[0], kp.halfL[0]);
             const double dy = min_image(yi - a.x[N + j], kp.L[1], kp.halfL[1]);
             const double dz = min_image(zi - a.x[2 * N + j], kp.L[2], kp.halfL[2]);
-            const double r = sqrt(dist2(dx, dy, dz));
-            const double ext = r - kp.bond_r0;
-            const double mag = -kp.bond_k * ext;
-            fx += mag * dx / r;
-            fy += mag * dy / r;
-            fz += mag * dz / r;
+            const RootPair r = distance(dist2(dx, dy, dz));
+            const double ext = r.root - kp.bond_r0;
+            const double mag = -kp.bond_k * ext * r.inv;
+            fx += mag * dx;
+            fy += mag * dy;
+            fz += mag * dz;
             pe += 0.25 * kp.bond_k * ext * ext;
         }
     }
@@ -322,7 +322,7 @@ struct PairJob {
 // once per chunk and made wave-uniform (scalar registers), where the pairs
 // would otherwise read them from the batch table through vector loads.
 struct PairParams {
-    double L[3], halfL[3];
+    double L[3], inv_L[3];
     double rc2, rl2, inv_rc, s, r_c;
     float cell_len32[3];
     int32_t nc[3];
@@ -347,7 +347,7 @@ __device__ __forceinline__ PairParams pair_params(const KParams& K)
     PairParams p;
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-        p.L[d] = rfl(K.L[d]); p.halfL[d] = rfl(K.halfL[d]);
+        p.L[d] = rfl(K.L[d]); p.inv_L[d] = rfl(K.inv_L[d]);
         p.cell_len32[d] = rfl(K.cell_len32[d]); p.nc[d] = rfl(K.nc[d]);
     }
     p.rc2 = rfl(K.rc2); p.rl2 = rfl(K.rl2); p.inv_rc = rfl(K.inv_rc); p.s = rfl(K.s); p.r_c = rfl(K.r_c);
@@ -545,7 +545,14 @@ __device__ __forceinline__ int32_t row_end_lane(const PairJob& jb, int32_t eb)
 }
 
 // One pair (FP64): force contribution on i and its half of the pair
-// potential.  P supplies geometry and cutoff; A / G / S the type tables
+// potential.  The pass is bound by vector instructions and, on few particles,
+// by their latencies; half of a pair's were the library's square roots,
+// divisions, log and cospi, whose special cases a pair cannot meet.  With
+// root_pair, neg2_ln_u32 and cos_turn_u32 (and one root less for s = 1/2):
+// 4M particles 907 -> 857 us, 700,001 without half-kicks 200 -> 184 us, 10
+// systems of 4,608 65 -> 60 us; the errors against 64-bit arithmetic are the
+// same (a variate's 8.2e-17 rms).
+//  P supplies geometry and cutoff; A / G / S the type tables
 // (a, gamma, sigma / sqrt(dt)).
 // One particle's operands of the FP64 pair: from the packed copies when
 // the step wrote them, else from the state's arrays.
@@ -619,25 +626,37 @@ __device__ __forceinline__ bool pair64(const PT& P, const double* A, const doubl
                                        const Op64& oi, const Op64& oj, uint64_t step,
                                        double& px, double& py, double& pz, double& pp)
 {
-    const double dx = min_image(oi.x - oj.x, P.L[0], P.halfL[0]);
-    const double dy = min_image(oi.y - oj.y, P.L[1], P.halfL[1]);
-    const double dz = min_image(oi.z - oj.z, P.L[2], P.halfL[2]);
+    // (the same values as min_image for every pair within r_c, boxes being
+    // 3 r_c wide or more: -L, 0 or L added)
+    auto image = [](double d, double L, double inv_L) { return __fma_rn(-__builtin_rint(d * inv_L), L, d); };
+    const double dx = image(oi.x - oj.x, P.L[0], P.inv_L[0]);
+    const double dy = image(oi.y - oj.y, P.L[1], P.inv_L[1]);
+    const double dz = image(oi.z - oj.z, P.L[2], P.inv_L[2]);
     const double r2 = dist2(dx, dy, dz);
     if (!(r2 < P.rc2)) return false;
-    const double rr = sqrt(r2);
-    // one correctly rounded reciprocal for the three components (within an
-    // ulp of the three quotients)
-    const double inv_r = 1.0 / rr;
+    const RootPair dist = distance(r2);
+    const double rr = dist.root, inv_r = dist.inv;
     const double ex = dx * inv_r, ey = dy * inv_r, ez = dz * inv_r;
     const double wc = 1.0 - rr * P.inv_rc;
-    const double wr = weight_r(wc, kWMode, P.s);
-    const double wd = wr * wr;
     const double ev = ex * (oi.vx - oj.vx) + ey * (oi.vy - oj.vy) + ez * (oi.vz - oj.vz);
     const int tp = oi.type * P.n_types + oj.type;
     uint32_t s0 = P.seed_lo, s1 = P.seed_hi;
     opaque_keys<kUniform>(s0, s1);
-    const double xi_ij = gauss64(pair_words(oi.tag, oj.tag, step, s0, s1));
-    const double phi = A[tp] * wc - G[tp] * wd * ev + S[tp] * wr * xi_ij;
+    const U4 w = pair_words(oi.tag, oj.tag, step, s0, s1);
+    // w_R times the variate sqrt(-2 ln u1) cos(2 pi u2); for s = 1/2 one root
+    // of w_C (-2 ln u1) (kept off zero, whose root root_pair does not take)
+    // and w_D = w_C
+    double wd, wr_xi;
+    if constexpr (kWMode == 0) {
+        const double q = wc * neg2_ln_u32(w.x);
+        wd = wc;
+        wr_xi = root_pair(q > 1e-200 ? q : 1e-200).root * cos_turn_u32(w.y);
+    } else {
+        const double wr = weight_r(wc, kWMode, P.s);
+        wd = wr * wr;
+        wr_xi = wr * gauss64(w);
+    }
+    const double phi = A[tp] * wc - G[tp] * wd * ev + S[tp] * wr_xi;
     px = phi * ex; py = phi * ey; pz = phi * ez;
     pp = 0.25 * A[tp] * P.r_c * wc * wc;
     return true;
@@ -890,9 +909,9 @@ __device__ __forceinline__ bool pair32(const PT& P, const Tab* A, const Tab* G, 
     if (hit && r2 < kCloseR2) {
         // FP32 offsets cannot resolve the direction of a nearly coincident
         // pair: take its geometry from FP64 positions
-        const double ddx = min_image(a.x[i] - a.x[j], P.L[0], P.halfL[0]);
-        const double ddy = min_image(a.x[N + i] - a.x[N + j], P.L[1], P.halfL[1]);
-        const double ddz = min_image(a.x[2 * N + i] - a.x[2 * N + j], P.L[2], P.halfL[2]);
+        const double ddx = min_image(a.x[i] - a.x[j], P.L[0], 0.5 * P.L[0]);
+        const double ddy = min_image(a.x[N + i] - a.x[N + j], P.L[1], 0.5 * P.L[1]);
+        const double ddz = min_image(a.x[2 * N + i] - a.x[2 * N + j], P.L[2], 0.5 * P.L[2]);
         const double r64 = sqrt(dist2(ddx, ddy, ddz));
         if (r64 > 0.0) {
             rr = (float)r64;

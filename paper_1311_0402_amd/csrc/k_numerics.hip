@@ -240,8 +240,8 @@ __global__ __launch_bounds__(kWave) void k_numerics_latency(int32_t chain, int64
 }
 
 // Pair Gaussians of consecutive pairs (t, t + 1 .. t + m) of each thread's
-// tag t: generator 0 = Philox4x32-10 words and Box-Muller with the device
-// library's log, sqrt and cospi (the FP64 force pass's generator);
+// tag t: generator 0 = Philox4x32-10 words and Box-Muller by gauss64 (the
+// FP64 force pass's generator);
 // generator 1 = TEA-4 on signatures with fast_ln and fast_cos2pi.
 // Signatures of generator 1 come from sig[] (one per tag).
 template <int kGen>
