@@ -290,7 +290,7 @@ namespace {
 int enqueue_reorder(const Job& job, const WsLayout& L, void* ws, const dpd_state* in,
                     const double* vt_in, dpd_state* out, double* vt_out, dpd_cells* cells,
                     float* x32, float* v32, hipStream_t s, bool aos = false, int32_t* inv = nullptr,
-                    bool write_iot = true)
+                    bool write_iot = true, const dpd_nlist* list_next = nullptr)
 {
     const int32_t n = in->n;
     int32_t* key = carve<int32_t>(ws, L.key);
@@ -315,19 +315,24 @@ int enqueue_reorder(const Job& job, const WsLayout& L, void* ws, const dpd_state
     g.x64 = aos ? carve<double>(ws, L.x64) : nullptr;
     g.v64 = aos ? carve<double>(ws, L.v64) : nullptr;
     g.xref = job.gate ? carve<double>(ws, L.xref) : nullptr;
+    // (list_next: enqueue_nlist follows, with `cleared`)
+    g.clear[0] = list_next ? list_next->offset + n : nullptr;
+    g.clear[1] = list_next ? carve<int32_t>(ws, L.slab_flag) : nullptr;
+    g.clear[2] = list_next ? carve<int32_t>(ws, L.tile_rest) : nullptr;
     DPD_TRY(launch_finalize(job.kp, job.bv, n, tmp_key, cells->cell_start, tmp_tag, tmp_src, g, s, gt), "finalize");
     return DPD_OK;
 }
 
 int enqueue_nlist(const Job& job, const WsLayout& L, void* ws, const dpd_state* st,
                   const dpd_cells* cells, const float* x32, dpd_nlist* nl, int32_t* d_status, hipStream_t s,
-                  bool compact = true)
+                  bool compact = true, bool cleared = false)
 {
     DPD_TRY(launch_nlist(job.kp, job.bv, job.n_cells, job.n_blocks, job.n_tiles, st->n, st->x, x32, cells->cell_xyz,
                          cells->cell_start, carve<int32_t>(ws, L.rank_tab), nl->offset, nl->index, nl->capacity,
                          carve<int32_t>(ws, L.slab), L.slab_k, carve<int32_t>(ws, L.slab_flag),
                          carve<int32_t>(ws, L.tile_rest), d_status,
-                         carve<int32_t>(ws, L.scan_part), job.nlist_waves, job.nlist_kind, compact, s, job.gate),
+                         carve<int32_t>(ws, L.scan_part), job.nlist_waves, job.nlist_kind, compact, s, job.gate,
+                         cleared),
             "neighbour list");
     return DPD_OK;
 }
@@ -475,9 +480,10 @@ int enqueue_batch_step(const dpd_batch* bt, const WsLayout& L, void* ws, int32_t
     int rc;
     DPD_TRY(launch_vv1(kp, job.bv, n, st->x, st->v, st->f, st->tag, st->type, b.x, b.v, bvt, b.tag, b.type, s),
             "vv1");
-    if ((rc = enqueue_reorder(job, L, ws, &b, bvt, st, vt_sorted, cells, x32, mixed ? v32 : nullptr, s, aos)))
+    if ((rc = enqueue_reorder(job, L, ws, &b, bvt, st, vt_sorted, cells, x32, mixed ? v32 : nullptr, s, aos,
+                              nullptr, true, nl)))
         return rc;
-    if ((rc = enqueue_nlist(job, L, ws, st, cells, x32, nl, d_status, s, false))) return rc;
+    if ((rc = enqueue_nlist(job, L, ws, st, cells, x32, nl, d_status, s, false, true))) return rc;
     DPD_TRY(launch_forces(kp, job.bv, precision, a, s), "forces");
     // the second half-kick (dt is shared by the systems) and the statistics
     // in one pass per 64-particle chunk
@@ -785,6 +791,7 @@ int dpd_step(const dpd_params* p, int32_t precision, dpd_state* st, int32_t n_st
     // lane of the force pass each.
     ForceArgs af = a;
     int32_t* kept_off = skin ? carve<int32_t>(ws, L.kept_off) : nullptr;
+    int32_t* kflag = skin ? carve<int32_t>(ws, L.kept_flag) : nullptr;
     if (skin) {
         af.slab = carve<int32_t>(ws, L.kept);
         af.slab_flag = carve<int32_t>(ws, L.kept_flag);
@@ -804,13 +811,17 @@ int dpd_step(const dpd_params* p, int32_t precision, dpd_state* st, int32_t n_st
         jk.gate = g;
         DPD_TRY(mark(k, 0), "event");
         if (k == 0) {
-            if (skin) DPD_TRY(launch_fill_i32(g, 1, 1, s), "rebuild flag");
+            if (skin) {
+                DPD_TRY(launch_fill_i32(g, 1, 1, s), "rebuild flag");
+                DPD_TRY(launch_zero3(kflag, kept_off + n, nullptr, s, nullptr), "kept rows flag and total");
+            }
             DPD_TRY(launch_vv1(kp, job.bv, n, st->x, st->v, st->f, st->tag, st->type, b.x, b.v, bvt, b.tag, b.type, s),
                     "vv1");
         } else if (fuse_vv) {
             // (the previous step's force pass did phase 2 and this phase 1)
         } else if (skin) {
-            DPD_TRY(launch_fill_i32(g, 1, 0, s), "rebuild flag");
+            // (the last step's force pass, which read the kept rows, is done)
+            DPD_TRY(launch_zero3(g, kflag, kept_off + n, s, nullptr), "rebuild flag, kept rows flag and total");
             sd.flag = g;
             DPD_TRY(launch_drift_skin(kp, n, sd, red_part, a.fred_part, force_grid(a), fsum_part, s), "vv2 + vv1");
             DPD_TRY(launch_reduce_final(n, red_part, kRedBlocks, fsum_part, kRedBlocks,
@@ -827,7 +838,7 @@ int dpd_step(const dpd_params* p, int32_t precision, dpd_state* st, int32_t n_st
         }
         DPD_TRY(mark(k, 1), "event");
         rc = enqueue_reorder(jk, L, ws, &b, bvt, st, vt_sorted, cells, x32, mixed ? v32 : nullptr, s, aos,
-                             k > 0 ? inv : nullptr, !bonds || skin || k == 0 || k == n_steps - 1);
+                             k > 0 ? inv : nullptr, !bonds || skin || k == 0 || k == n_steps - 1, nl);
         if (rc) return rc;
         if (bonds) {
             if (k == 0) {
@@ -841,15 +852,12 @@ int dpd_step(const dpd_params* p, int32_t precision, dpd_state* st, int32_t n_st
         DPD_TRY(mark(k, 2), "event");
         // inside a call the force pass reads the builder's slab; the CSR list
         // is written for the last step, which the caller sees
-        rc = enqueue_nlist(jk, L, ws, st, cells, x32, nl, d_status, s, k == n_steps - 1);
+        rc = enqueue_nlist(jk, L, ws, st, cells, x32, nl, d_status, s, k == n_steps - 1, true);
         if (rc) return rc;
         if (skin) {
             af.pidx = a.pidx;
-            int32_t* kflag = carve<int32_t>(ws, L.kept_flag);
-            DPD_TRY(launch_fill_i32(kflag, 1, 0, s), "kept rows flag");
             DPD_TRY(launch_skin_filter(kp, precision, a, carve<int32_t>(ws, L.kept), kept_off, kflag, s),
                     "rows inside r_c");
-            DPD_TRY(launch_fill_i32(kept_off + n, 1, 0, s), "kept rows total");
             DPD_TRY(launch_scan(kept_off, (int64_t)n + 1, carve<int32_t>(ws, L.scan_part), s), "kept rows scan");
         }
         DPD_TRY(mark(k, 3), "event");

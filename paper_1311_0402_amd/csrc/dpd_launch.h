@@ -62,6 +62,7 @@ hipError_t launch_bin(const KParams& kp, const BatchView& bv, int32_t n, const d
                       int32_t* key, int32_t* slot, uint32_t* cxyz, int32_t* counts, hipStream_t s,
                       Gate gate = nullptr);
 // in-place exclusive scan of data[0 .. count); partials needs ceil(count/kScanTile) ints
+// (1 to 3 launches by size)
 hipError_t launch_scan(int32_t* data, int64_t count, int32_t* partials, hipStream_t s, Gate gate = nullptr);
 hipError_t launch_place(int32_t n, const int32_t* key, const int32_t* slot, const int32_t* cell_start,
                         const uint32_t* tag, uint32_t* tmp_tag, int32_t* tmp_src, int32_t* tmp_key, hipStream_t s,
@@ -75,6 +76,7 @@ struct GatherArgs {
     float* x32; float* v32;
     double* x64; double* v64;       // nullable: packed FP64 copies, double4 per particle
     double* xref = nullptr;         // nullable: a second copy of the sorted positions ([3][n])
+    int32_t* clear[3];         // counters of the list build that follows, set to zero, or null
 };
 // bond partners of the sorted particles as sorted indices: pidx[2 i + b] =
 // idx_of_tag[partner[2 tag[i] + b]], -1 without a partner, -2 when the
@@ -108,13 +110,14 @@ constexpr int32_t kSlabJMask = (1 << kSlabCodeShift) - 1;
 // kind 0: tile builder, 1: block builder, 2: lane builder (0 and 2 need
 // cell_xyz and fewer than 2^27 cells, else the block builder runs); waves
 // sizes the workgroups of builders 1 and 2; tile_rest (n_tiles + 1 ints)
-// lists the tiles the tile builder leaves to the lane builder.
+// lists the tiles the tile builder leaves to the lane builder.  cleared: the
+// reorder before has set offset[n], *flag and tile_rest[0] to zero.
 hipError_t launch_nlist(const KParams& kp, const BatchView& bv, int32_t n_cells, int32_t n_blocks, int32_t n_tiles,
                         int32_t n, const double* x, const float* x32, const uint32_t* cell_xyz,
                         const int32_t* cell_start, const int32_t* rank_tab, int32_t* offset, int32_t* index,
                         int64_t capacity, int32_t* slab, int32_t slab_k, int32_t* flag, int32_t* tile_rest,
                         int32_t* status, int32_t* scan_part, int waves, int kind, bool compact, hipStream_t s,
-                        Gate gate = nullptr);
+                        Gate gate = nullptr, bool cleared = false);
 // whether that build leaves coded slab entries (tile and lane builders, n < 2^26)
 bool nlist_slab_coded(int kind, const uint32_t* cell_xyz, int32_t n_cells, int32_t n);
 // waves per workgroup of the tile builder for n particles in n_cells cells

@@ -71,6 +71,15 @@ __device__ __forceinline__ bool exact_hit(const KParams& kp, const double* __res
     return dist2(dx, dy, dz) < kp.rl2;
 }
 
+// the direct pass's launch, which every build ends with, also says whether
+// the list fits
+__device__ __forceinline__ void capacity_check(const int32_t* __restrict__ offset, int32_t n, int64_t capacity,
+                                               int32_t* __restrict__ status)
+{
+    if (status && blockIdx.x == 0 && threadIdx.x == 0 && (int64_t)offset[n] > capacity)
+        atomicOr(status, 1 /* DPD_STATUS_NLIST_OVERFLOW */);
+}
+
 // kDirect = false: rows go to a fixed-width scratch slab (row i at
 // slab[i * K]) and row sizes to offset[]; a scan and k_nlist_compact then
 // produce the CSR list.  kDirect = true: the same walk writes straight into
@@ -222,9 +231,11 @@ __global__ __launch_bounds__(kW * kWave) void k_nlist(KParams kp, BatchView bv, 
                                                       const int32_t* __restrict__ rank_tab,
                                                       int32_t* __restrict__ offset, int32_t* __restrict__ index,
                                                       int64_t capacity, int32_t* __restrict__ slab, int32_t slab_k,
-                                                      int32_t* __restrict__ flag, Gate gate)
+                                                      int32_t* __restrict__ flag, int32_t* __restrict__ status,
+                                                      Gate gate)
 {
     if (gated_off(gate)) return;
+    if constexpr (kDirect) capacity_check(offset, n, capacity, status);
     const int32_t blk = xcd_logical_id(blockIdx.x, gridDim.x) * kW + threadIdx.x / kWave;
     if (blk >= n_blocks) return;
     if (kDirect && (*flag == 0 || (int64_t)offset[n] > capacity)) return;
@@ -343,9 +354,11 @@ __global__ __launch_bounds__(kW * kWave) void k_nlist_lanes(KParams kp, BatchVie
                                                             int32_t* __restrict__ offset,
                                                             int32_t* __restrict__ index, int64_t capacity,
                                                             int32_t* __restrict__ slab, int32_t slab_k,
-                                                            int32_t* __restrict__ flag, Gate gate)
+                                                            int32_t* __restrict__ flag,
+                                                            int32_t* __restrict__ status, Gate gate)
 {
     if (gated_off(gate)) return;
+    if constexpr (kDirect) capacity_check(offset, n, capacity, status);
     if (kDirect && (*flag == 0 || (int64_t)offset[n] > capacity)) return;
     // (the direct pass runs on a capped grid, each lane taking every
     // gridDim-th group of rows: it is launched for every build and returns
@@ -367,65 +380,65 @@ template <bool kDirect, int kW>
 void launch_nlist_lanes(const KParams& kp, const BatchView& bv, int32_t n, const double* x, const float* x32,
                         const uint32_t* cell_xyz, const int32_t* cell_start, const int32_t* rank_tab,
                         int32_t* offset, int32_t* index, int64_t capacity, int32_t* slab, int32_t slab_k,
-                        int32_t* flag, hipStream_t s, Gate gate)
+                        int32_t* flag, int32_t* status, hipStream_t s, Gate gate)
 {
     const int32_t blocks = ceil_div(n, kW * kWave);
     const dim3 grid(kDirect && blocks > kDirectGrid ? kDirectGrid : blocks), block(kW * kWave);
     if (bv.kps)
         hipLaunchKernelGGL((k_nlist_lanes<kDirect, true, kW>), grid, block, 0, s, kp, bv, n, x, x32, cell_xyz,
-                           cell_start, rank_tab, offset, index, capacity, slab, slab_k, flag, gate);
+                           cell_start, rank_tab, offset, index, capacity, slab, slab_k, flag, status, gate);
     else
         hipLaunchKernelGGL((k_nlist_lanes<kDirect, false, kW>), grid, block, 0, s, kp, bv, n, x, x32, cell_xyz,
-                           cell_start, rank_tab, offset, index, capacity, slab, slab_k, flag, gate);
+                           cell_start, rank_tab, offset, index, capacity, slab, slab_k, flag, status, gate);
 }
 
 template <bool kDirect>
 void launch_nlist_lanes(int waves, const KParams& kp, const BatchView& bv, int32_t n, const double* x,
                         const float* x32, const uint32_t* cell_xyz, const int32_t* cell_start,
                         const int32_t* rank_tab, int32_t* offset, int32_t* index, int64_t capacity,
-                        int32_t* slab, int32_t slab_k, int32_t* flag, hipStream_t s, Gate gate)
+                        int32_t* slab, int32_t slab_k, int32_t* flag, int32_t* status, hipStream_t s, Gate gate)
 {
     if (waves == 1)
         launch_nlist_lanes<kDirect, 1>(kp, bv, n, x, x32, cell_xyz, cell_start, rank_tab, offset, index, capacity,
-                                       slab, slab_k, flag, s, gate);
+                                       slab, slab_k, flag, status, s, gate);
     else if (waves == 2)
         launch_nlist_lanes<kDirect, 2>(kp, bv, n, x, x32, cell_xyz, cell_start, rank_tab, offset, index, capacity,
-                                       slab, slab_k, flag, s, gate);
+                                       slab, slab_k, flag, status, s, gate);
     else
         launch_nlist_lanes<kDirect, 4>(kp, bv, n, x, x32, cell_xyz, cell_start, rank_tab, offset, index, capacity,
-                                       slab, slab_k, flag, s, gate);
+                                       slab, slab_k, flag, status, s, gate);
 }
 
 template <bool kDirect, int kW>
 void launch_nlist_pass(const KParams& kp, const BatchView& bv, int32_t n_blocks, int32_t n, const double* x,
                        const float* x32, const int32_t* cell_start, const int32_t* rank_tab, int32_t* offset,
                        int32_t* index, int64_t capacity, int32_t* slab, int32_t slab_k, int32_t* flag,
-                       hipStream_t s, Gate gate)
+                       int32_t* status, hipStream_t s, Gate gate)
 {
     const dim3 grid(ceil_div(n_blocks, kW)), block(kW * kWave);
     if (bv.kps)
         hipLaunchKernelGGL((k_nlist<kDirect, true, kW>), grid, block, 0, s, kp, bv, n_blocks, n, x, x32, cell_start,
-                           rank_tab, offset, index, capacity, slab, slab_k, flag, gate);
+                           rank_tab, offset, index, capacity, slab, slab_k, flag, status, gate);
     else
         hipLaunchKernelGGL((k_nlist<kDirect, false, kW>), grid, block, 0, s, kp, bv, n_blocks, n, x, x32,
-                           cell_start, rank_tab, offset, index, capacity, slab, slab_k, flag, gate);
+                           cell_start, rank_tab, offset, index, capacity, slab, slab_k, flag, status, gate);
 }
 
 template <bool kDirect>
 void launch_nlist_pass(int waves, const KParams& kp, const BatchView& bv, int32_t n_blocks, int32_t n,
                        const double* x, const float* x32, const int32_t* cell_start, const int32_t* rank_tab,
                        int32_t* offset, int32_t* index, int64_t capacity, int32_t* slab, int32_t slab_k,
-                       int32_t* flag, hipStream_t s, Gate gate)
+                       int32_t* flag, int32_t* status, hipStream_t s, Gate gate)
 {
     if (waves == 1)
         launch_nlist_pass<kDirect, 1>(kp, bv, n_blocks, n, x, x32, cell_start, rank_tab, offset, index, capacity,
-                                      slab, slab_k, flag, s, gate);
+                                      slab, slab_k, flag, status, s, gate);
     else if (waves == 2)
         launch_nlist_pass<kDirect, 2>(kp, bv, n_blocks, n, x, x32, cell_start, rank_tab, offset, index, capacity,
-                                      slab, slab_k, flag, s, gate);
+                                      slab, slab_k, flag, status, s, gate);
     else
         launch_nlist_pass<kDirect, 4>(kp, bv, n_blocks, n, x, x32, cell_start, rank_tab, offset, index, capacity,
-                                      slab, slab_k, flag, s, gate);
+                                      slab, slab_k, flag, status, s, gate);
 }
 
 // ---- tile builder ----
@@ -1084,13 +1097,13 @@ hipError_t launch_nlist(const KParams& kp, const BatchView& bv, int32_t n_cells,
                         const int32_t* cell_start, const int32_t* rank_tab, int32_t* offset, int32_t* index,
                         int64_t capacity, int32_t* slab, int32_t slab_k, int32_t* flag, int32_t* tile_rest,
                         int32_t* status, int32_t* scan_part, int waves, int kind, bool compact, hipStream_t s,
-                        Gate gate)
+                        Gate gate, bool cleared)
 {
     if (n <= 0) return hipSuccess;
     hipError_t e;
     const bool tiles = kind == 0 && ranks_fit(cell_xyz, n_cells);
     const bool lanes = tiles || (kind == 2 && ranks_fit(cell_xyz, n_cells));
-    if ((e = launch_zero3(offset + n, flag, tiles ? tile_rest : nullptr, s, gate)) != hipSuccess) return e;
+    if (!cleared && (e = launch_zero3(offset + n, flag, tiles ? tile_rest : nullptr, s, gate)) != hipSuccess) return e;
     if (tiles) {
         const int tw = nlist_tile_waves(n, n_cells);
         if (bv.kps)
@@ -1101,15 +1114,11 @@ hipError_t launch_nlist(const KParams& kp, const BatchView& bv, int32_t n_cells,
                                       slab_k, flag, tile_rest, s, gate);
     } else if (lanes)
         launch_nlist_lanes<false>(waves, kp, bv, n, x, x32, cell_xyz, cell_start, rank_tab, offset, index, capacity,
-                                  slab, slab_k, flag, s, gate);
+                                  slab, slab_k, flag, status, s, gate);
     else
         launch_nlist_pass<false>(waves, kp, bv, n_blocks, n, x, x32, cell_start, rank_tab, offset, index, capacity,
-                                 slab, slab_k, flag, s, gate);
+                                 slab, slab_k, flag, status, s, gate);
     if ((e = launch_scan(offset, (int64_t)n + 1, scan_part, s, gate)) != hipSuccess) return e;
-    if (status) {
-        hipLaunchKernelGGL(k_nlist_check, dim3(1), dim3(64), 0, s, n, (const int32_t*)offset, capacity, status, gate);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
     // without compaction the CSR index is left unwritten unless a row
     // overflowed the slab (then the direct pass below writes it).  The
     // compaction takes no gate: after a step that kept the last build's
@@ -1118,14 +1127,15 @@ hipError_t launch_nlist(const KParams& kp, const BatchView& bv, int32_t n_cells,
         hipLaunchKernelGGL(k_nlist_compact, dim3(ceil_div(ceil_div(n, kWave), kWavesPerBlock)), dim3(kBlock), 0,
                            s, n, (const int32_t*)offset, capacity, (const int32_t*)slab, slab_k,
                            (const int32_t*)flag, index);
-    // rows that overflowed the slab: the lane builder's walk writes the CSR
-    // rows directly (the same rows the tile builder would give)
+    // the capacity check, and rows that overflowed the slab: the lane builder's
+    // walk writes the CSR rows directly (the same rows the tile builder would
+    // give)
     if (lanes)
         launch_nlist_lanes<true>(waves, kp, bv, n, x, x32, cell_xyz, cell_start, rank_tab, offset, index, capacity,
-                                 slab, slab_k, flag, s, gate);
+                                 slab, slab_k, flag, status, s, gate);
     else
         launch_nlist_pass<true>(waves, kp, bv, n_blocks, n, x, x32, cell_start, rank_tab, offset, index, capacity,
-                                slab, slab_k, flag, s, gate);
+                                slab, slab_k, flag, status, s, gate);
     return hipGetLastError();
 }
 

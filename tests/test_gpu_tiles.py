@@ -71,3 +71,21 @@ def test_positions_that_are_no_numbers_have_no_neighbours():
     np.testing.assert_array_equal(off, off_ref)
     np.testing.assert_array_equal(idx, idx_ref)
     assert np.count_nonzero(np.diff(off) == 0) >= bad.size
+
+
+@pytest.mark.parametrize("n", [1, 4095, 4096, 1024 * 4096 - 1, 1024 * 4096])
+def test_offsets_at_the_scans_edges(n):
+    """The scan of the n + 1 row sizes in one launch (to 4,096 items), in two
+    (to 1,024 workgroups' 4,096 items) and in three: offsets of a seeded sample
+    of rows, and their number, against the oracle's rows and the row lengths."""
+    side = max(3.3, (n / 3.0) ** (1.0 / 3.0))
+    s = di.uniform_fluid(n, (side,) * 3, 55)
+    x, off, idx = _rows(s)
+    assert off[0] == 0 and off[-1] == len(idx) and np.all(np.diff(off) >= 0)
+    q = np.unique(np.concatenate([np.random.default_rng(55).choice(n, min(n, 60), replace=False), [0, n - 1]]))
+    off_ref, idx_ref = oracle.neighbors(x, s.box, s.r_c, query=q.astype(np.int32))
+    for k, i in enumerate(q):
+        np.testing.assert_array_equal(idx[off[i]:off[i + 1]], idx_ref[off_ref[k]:off_ref[k + 1]], err_msg=f"row {i}")
+    # every offset: rows ascend, so the list falls at row ends only
+    down = np.nonzero(np.diff(idx) <= 0)[0] + 1
+    assert np.all(np.isin(down, off))
