@@ -950,9 +950,14 @@ __global__ __launch_bounds__(kW * kWave) void k_nlist_tiles(KParams kp, BatchVie
 
 // Tiles the tile builder left (neighbourhood over the LDS capacity):
 // rest[0] tiles listed in rest[1..], their particles walked by the lane
-// builder.
+// builder.  A lane's walk is one serial chain of some 60 us, and the tiles are
+// few: one wave per workgroup, kRestParts of them to a tile, so that each
+// lane walks one row (256 systems, of which the smallest leave some tiles:
+// 125 us with a tile to a workgroup of four waves, in two rounds, 89 us now).
+constexpr int kRestParts = 8;
+
 template <bool kB>
-__global__ __launch_bounds__(kBlock) void k_nlist_tile_rest(KParams kp, BatchView bv, int32_t n,
+__global__ __launch_bounds__(kWave) void k_nlist_tile_rest(KParams kp, BatchView bv, int32_t n,
                                                             const double* __restrict__ x,
                                                             const float* __restrict__ x32,
                                                             const uint32_t* __restrict__ cell_xyz,
@@ -964,10 +969,11 @@ __global__ __launch_bounds__(kBlock) void k_nlist_tile_rest(KParams kp, BatchVie
                                                             const int32_t* __restrict__ rest, Gate gate)
 {
     if (gated_off(gate)) return;
-    const int32_t count = rest[0];
-    for (int32_t t = blockIdx.x; t < count; t += gridDim.x) {
-        const TileGeom g = tile_geom<kB>(kp, bv, rest[1 + t], cell_start, rank_tab);
-        for (int32_t i = g.i_lo + (int32_t)threadIdx.x; i < g.i_hi; i += kBlock)
+    const int64_t count = (int64_t)rest[0] * kRestParts;
+    for (int64_t t = blockIdx.x; t < count; t += gridDim.x) {
+        const TileGeom g = tile_geom<kB>(kp, bv, rest[1 + t / kRestParts], cell_start, rank_tab);
+        const int32_t first = g.i_lo + (int32_t)(t % kRestParts) * kWave;
+        for (int32_t i = first + (int32_t)threadIdx.x; i < g.i_hi; i += kRestParts * kWave)
             nlist_lane<false>(*g.P, i, n, x, x32, cell_xyz, cell_start, rank_tab, offset, nullptr, slab, slab_k,
                               flag);
     }
@@ -990,7 +996,8 @@ void launch_nlist_tiles(int waves, const KParams& kp, const BatchView& bv, int32
                         const int32_t* rank_tab, int32_t* offset, int32_t* slab, int32_t slab_k, int32_t* flag,
                         int32_t* rest, hipStream_t s, Gate gate)
 {
-    // Workgroups sharing a compute unit: as many as its 32 waves allow, but
+    // Workgroups sharing a compute unit: as many as its 32 waves allow (8 waves:
+    // four 444 us, three with more words a lane 561 us, for the 256 systems), but
     // one of 16 waves, with 32 words a lane against 18, where each of the 256
     // units gets two tiles at most (10 systems of 4,608 particles, 180 tiles:
     // 46.6 and 54.4 us; 1M particles at r_c + skin, 1,200 tiles: 85 and 84 us,
@@ -1000,14 +1007,14 @@ void launch_nlist_tiles(int waves, const KParams& kp, const BatchView& bv, int32
                                    slab_k, flag, rest, s, gate)
     if (waves <= 6) DPD_TILE_CASE(6, 4);
     else if (waves <= 7) DPD_TILE_CASE(7, 4);
-    else if (waves <= 8) DPD_TILE_CASE(8, 3);
+    else if (waves <= 8) DPD_TILE_CASE(8, 4);
     else if (waves <= 10) DPD_TILE_CASE(10, 3);
     else if (waves <= 12) DPD_TILE_CASE(12, 2);
     else if (n_tiles > 512) DPD_TILE_CASE(16, 2);
     else DPD_TILE_CASE(16, 1);
 #undef DPD_TILE_CASE
-    const int grid = n_tiles < 1024 ? n_tiles : 1024;
-    hipLaunchKernelGGL((k_nlist_tile_rest<kB>), dim3(grid), dim3(kBlock), 0, s, kp, bv, n, x, x32, cell_xyz,
+    const int grid = n_tiles < 512 ? n_tiles * kRestParts : 512 * kRestParts;
+    hipLaunchKernelGGL((k_nlist_tile_rest<kB>), dim3(grid), dim3(kWave), 0, s, kp, bv, n, x, x32, cell_xyz,
                        cell_start, rank_tab, offset, slab, slab_k, flag, (const int32_t*)rest, gate);
 }
 
