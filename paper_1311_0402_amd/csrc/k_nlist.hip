@@ -465,10 +465,10 @@ void launch_nlist_pass(int waves, const KParams& kp, const BatchView& bv, int32_
 // band that their rounding leaves open the FP64 rule decides (0.01 candidates
 // per particle at density 3).
 //
-// What bounds it: vector instructions.  A wave's instruction takes a SIMD four
-// clocks, and at 16M particles (density 3) ~2,600 of them per wave fill 88 %
-// of the time: the walk 40 % (8 instructions of distance test and 9 others
-// per four candidates), writing the rows 26 %, the sort and the runs 18 %.
+// What bounds it: instruction issue.  At 16M particles (density 3) a wave
+// takes ~2,700 vector instructions, one per 4.3 clocks and SIMD: the walk 40 %
+// (33 per step of four candidates, 23 of them the distance test),
+// writing the rows 26 %, the sort and the runs 18 %.
 // Hence the wide steps, the joined runs and the integer test; a list of steps
 // rather than of runs keeps the walk free of run ends (30 instructions per
 // step fewer); rows leave two entries at a time since scattered stores cost
