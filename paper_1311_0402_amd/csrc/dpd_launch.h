@@ -126,8 +126,6 @@ int nlist_tile_waves(int32_t n, int32_t n_cells);
 // is set: the direct pass wrote the rows then)
 hipError_t launch_nlist_compact(int32_t n, const int32_t* offset, int64_t capacity, const int32_t* slab,
                                 int32_t slab_k, const int32_t* flag, int32_t* index, hipStream_t s);
-hipError_t launch_nlist_check(int32_t n, const int32_t* offset, int64_t capacity, int32_t* status,
-                              hipStream_t s);
 
 // ---- forces (k_force.hip) ----
 // the next step's phase 1 fused after phase 2: bx, bv (, bvt) from x and

@@ -1067,14 +1067,6 @@ __global__ __launch_bounds__(kBlock) void k_nlist_compact(int32_t n, const int32
     }
 }
 
-__global__ void k_nlist_check(int32_t n, const int32_t* __restrict__ offset, int64_t capacity,
-                              int32_t* __restrict__ status, Gate gate)
-{
-    if (gated_off(gate)) return;
-    if (threadIdx.x == 0 && blockIdx.x == 0 && (int64_t)offset[n] > capacity)
-        atomicOr(status, 1 /* DPD_STATUS_NLIST_OVERFLOW */);
-}
-
 }  // namespace
 
 // Slots per row of the scratch slab: about 2.5 times the mean neighbour
@@ -1152,14 +1144,6 @@ hipError_t launch_nlist_compact(int32_t n, const int32_t* offset, int64_t capaci
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_nlist_compact, dim3(ceil_div(ceil_div(n, kWave), kWavesPerBlock)), dim3(kBlock), 0, s, n,
                        offset, capacity, slab, slab_k, flag, index);
-    return hipGetLastError();
-}
-
-hipError_t launch_nlist_check(int32_t n, const int32_t* offset, int64_t capacity, int32_t* status,
-                              hipStream_t s)
-{
-    if (!status) return hipSuccess;
-    hipLaunchKernelGGL(k_nlist_check, dim3(1), dim3(64), 0, s, n, offset, capacity, status, nullptr);
     return hipGetLastError();
 }
 
