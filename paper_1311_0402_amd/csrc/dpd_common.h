@@ -320,6 +320,18 @@ __device__ __forceinline__ RootPair distance(double r2)
     return o;
 }
 
+// w_C = 1 - r / r_c of a pair inside r_c.  Its r can round to r_c (root_pair
+// may round the last distance below up; with r_c != 1 so may the product with
+// the rounded 1 / r_c, even past 1), where w_C would be 0 and the backward
+// pass's w_R / w_C no number: such a pair stands at the last number below,
+// w_C = 2^-53, where the correctly rounded root puts it for r_c = 1.  (Values
+// above 0 are 2^-53 or more: any bound between them and 0 serves.)
+__device__ __forceinline__ double weight_c(double r, double inv_rc)
+{
+    const double wc = 1.0 - r * inv_rc;
+    return wc > 1e-17 ? wc : 0x1p-53;
+}
+
 // -2 ln u, u = (w + 1/2) 2^-32: u = m 2^e with m in [sqrt(1/2), sqrt(2)),
 // ln m = 2 atanh(s), s = (m - 1) / (m + 1), |s| < 0.172, by its series to
 // s^21 (remainder below 2^-57 of the sum); ln 2 in two parts, the first of 41

@@ -76,7 +76,7 @@ __global__ __launch_bounds__(kBlock) void k_force_bwd(KParams kp, BackwardArgs a
                 const int tyj = a.type[j];
                 const int tp = tyi * nt + tyj;
                 const double A = kp.a[tp], G = kp.g[tp], SR = kp.srdt[tp];
-                const double wc = 1.0 - r * kp.inv_rc;
+                const double wc = weight_c(r, kp.inv_rc);
                 const double wr = weight_r(wc, kWMode, kp.s);
                 const double wd = wr * wr;
                 const double dwc = -kp.inv_rc;

@@ -652,20 +652,18 @@ __device__ __forceinline__ bool pair64(const PT& P, const double* A, const doubl
     const RootPair dist = distance(r2);
     const double rr = dist.root, inv_r = dist.inv;
     const double ex = dx * inv_r, ey = dy * inv_r, ez = dz * inv_r;
-    const double wc = 1.0 - rr * P.inv_rc;
+    const double wc = weight_c(rr, P.inv_rc);
     const double ev = ex * (oi.vx - oj.vx) + ey * (oi.vy - oj.vy) + ez * (oi.vz - oj.vz);
     const int tp = oi.type * P.n_types + oj.type;
     uint32_t s0 = P.seed_lo, s1 = P.seed_hi;
     opaque_keys<kUniform>(s0, s1);
     const U4 w = pair_words(oi.tag, oj.tag, step, s0, s1);
     // w_R times the variate sqrt(-2 ln u1) cos(2 pi u2); for s = 1/2 one root
-    // of w_C (-2 ln u1) (kept off zero, whose root root_pair does not take)
-    // and w_D = w_C
+    // of w_C (-2 ln u1), which is above 0, and w_D = w_C
     double wd, wr_xi;
     if constexpr (kWMode == 0) {
-        const double q = wc * neg2_ln_u32(w.x);
         wd = wc;
-        wr_xi = root_pair(q > 1e-200 ? q : 1e-200).root * cos_turn_u32(w.y);
+        wr_xi = root_pair(wc * neg2_ln_u32(w.x)).root * cos_turn_u32(w.y);
     } else {
         const double wr = weight_r(wc, kWMode, P.s);
         wd = wr * wr;
