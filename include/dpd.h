@@ -106,7 +106,12 @@ typedef struct dpd_params {
 typedef struct dpd_state {
     int32_t n;
     int32_t reserved0;
-    double* x;              /* [3][n], each component in [0, L)                 */
+    double* x;              /* [3][n], each component in [0, L).  A value outside
+                               is not checked: the particle is binned into the
+                               nearest cell and listed by its geometry from
+                               there (dpd_step wraps by one box length a step,
+                               so a particle faster than that can stay outside);
+                               one that is no number has no neighbours           */
     double* v;              /* [3][n]                                            */
     double* f;              /* [3][n]                                            */
     uint32_t* tag;          /* [n]                                               */

@@ -483,8 +483,8 @@ void launch_nlist_pass(int waves, const KParams& kp, const BatchView& bv, int32_
 // appear in the union at two places, as two periodic images, and is staged
 // twice; every tile cell's 27 stencil cells are still distinct cells (3 or
 // more per side), each at the image next to it, so no candidate is seen
-// twice.  Tiles whose neighbourhood overflows the LDS take the lane
-// builder's walk over global memory.
+// twice.  Tiles whose neighbourhood overflows the LDS, or holds a particle
+// outside its cell, take the lane builder's walk over global memory.
 
 constexpr int kTUX = kTileX + 2, kTUY = kTileY + 2, kTUZ = kTileZ + 2;
 constexpr int kTU = kTUX * kTUY * kTUZ;          // union cells of a tile
@@ -514,7 +514,8 @@ struct TileLds {
     uint32_t range[kTU];                        // its slots: start | end << 12
     uint32_t cstep[kTC];                        // steps of a tile cell: first | number << 16
     int32_t sum[2][kW];
-    uint8_t off[32];                            // a stencil cell's place among the union cells
+    uint8_t off[28];                            // a stencil cell's place among the union cells
+    uint32_t outside;                           // whether a particle is not in its cell
     alignas(16) uint16_t step[tile_steps<kW>()];            // first slot << 4 | four bits, the slots of the run
     alignas(16) uint16_t word[kWords_ * kW * kWave];
 };
@@ -558,27 +559,30 @@ constexpr UnionOrder make_union_order()
 }
 __constant__ const UnionOrder kUnionOrder = make_union_order();
 
-// A slot: the particle's position in the walk's units, x | y << 16 and z, and
-// in the high half of the second word its union cell (9 bits) with the low
-// two bits of the cell's coordinates (6 bits, as in the slab's code).  A
-// particle that is not in its cell (a position that is no number, or outside
-// the box) has no neighbours: it stands 2.51 cells above its cell's middle,
-// more than 1.009 cells in z from whatever is compared with it (and so that
-// the squared distance stays below 2^31), and the top bit says so.
+// Whether a particle is in its cell, to a thousandth of it.  One that is not
+// (a position outside the box, binned into the nearest cell, or no number) may
+// be further from others than the walk's units span: its tiles are left to the
+// lane builder, which lists it by its geometry.
+__device__ __forceinline__ bool in_cell(const KParams& P, const float4& w)
+{
+    const float c0 = P.cell_len32[0], c1 = P.cell_len32[1], c2 = P.cell_len32[2];
+    return fabsf(w.x - 0.5f * c0) <= 0.501f * c0 && fabsf(w.y - 0.5f * c1) <= 0.501f * c1 &&
+           fabsf(w.z - 0.5f * c2) <= 0.501f * c2;
+}
+
+// A slot: the position of a particle in its cell in the walk's units, x | y << 16
+// and z, and in the high half of the second word its union cell (9 bits) with the
+// low two bits of the cell's coordinates (6 bits, as in the slab's code).
 typedef int16_t i16x2 __attribute__((ext_vector_type(2)));
 typedef int32_t i32x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint2 walk_pos(const KParams& P, const float4& w, int32_t ux, int32_t uy, int32_t uz,
                                           uint32_t cell)
 {
     const float c0 = P.cell_len32[0], c1 = P.cell_len32[1], c2 = P.cell_len32[2], inv = P.tile_inv;
-    const float mx = 0.5f * c0, my = 0.5f * c1, mz = 0.5f * c2;
-    const bool in = fabsf(w.x - mx) <= 0.501f * c0 && fabsf(w.y - my) <= 0.501f * c1 &&
-                    fabsf(w.z - mz) <= 0.501f * c2;
-    const int32_t x = (int32_t)__builtin_rintf(((in ? w.x : mx) + (float)(ux - kTFX) * c0) * inv),
-                  y = (int32_t)__builtin_rintf(((in ? w.y : my) + (float)(uy - kTFY) * c1) * inv),
-                  z = (int32_t)__builtin_rintf(((in ? w.z : mz) + (float)(uz - kTFZ) * c2) * inv);
-    return make_uint2(((uint32_t)x & 0xFFFFu) | ((uint32_t)y << 16),
-                      (((uint32_t)z & 0xFFFFu) | cell << 16) ^ (in ? 0u : 0x80008000u));
+    const int32_t x = (int32_t)__builtin_rintf((w.x + (float)(ux - kTFX) * c0) * inv),
+                  y = (int32_t)__builtin_rintf((w.y + (float)(uy - kTFY) * c1) * inv),
+                  z = (int32_t)__builtin_rintf((w.z + (float)(uz - kTFZ) * c2) * inv);
+    return make_uint2(((uint32_t)x & 0xFFFFu) | ((uint32_t)y << 16), ((uint32_t)z & 0xFFFFu) | cell << 16);
 }
 
 // squared distance plus neg_lo
@@ -694,6 +698,7 @@ __global__ __launch_bounds__(kW * kWave) void k_nlist_tiles(KParams kp, BatchVie
     const bool fits = (int64_t)(g.i_hi - g.i_lo) * slab_k * 4 + 4 * kTilePos < INT32_MAX;
 
     if (tid < 27) lds.off[tid] = (uint8_t)(tid % 3 + kTUX * (tid / 3 % 3 + kTUY * (tid / 9)));
+    if (tid == 27) lds.outside = 0u;
 
     // ---- union cells: thread t owns the t-th in LDS ----
     int32_t cnt = 0, u = 0;
@@ -746,8 +751,10 @@ __global__ __launch_bounds__(kW * kWave) void k_nlist_tiles(KParams kp, BatchVie
             const int32_t p = tid - kTC + q * kStagers, c = cell[q];
             const int32_t ux = c % kTUX, uy = (c / kTUX) % kTUY, uz = c / (kTUX * kTUY);
             const uint32_t code = (uint32_t)(ux & 3) | (uint32_t)(uy & 3) << 2 | (uint32_t)(uz & 3) << 4;
-            if (p < total)
-                lds.q[p] = walk_pos(P, w[q], ux, uy, uz, (uint32_t)c | code << 9);
+            if (p < total) {
+                if (in_cell(P, w[q])) lds.q[p] = walk_pos(P, w[q], ux, uy, uz, (uint32_t)c | code << 9);
+                else lds.outside = 1u;
+            }
         }
     }
 
@@ -791,7 +798,7 @@ __global__ __launch_bounds__(kW * kWave) void k_nlist_tiles(KParams kp, BatchVie
     }
     int32_t n_steps;
     const int32_t at_step = tile_excl_scan<kW>(m, lds.sum[1], n_steps);
-    if (n_steps > kSteps) {
+    if (n_steps > kSteps || lds.outside) {
         if (tid == 0) rest[1 + atomicAdd(rest, 1)] = tile;
         return;
     }
@@ -848,11 +855,10 @@ __global__ __launch_bounds__(kW * kWave) void k_nlist_tiles(KParams kp, BatchVie
         const int32_t self = i - lds.gl[(lx + 1) + kTUX * ((ly + 1) + kTUY * (lz + 1))];
         const uint2 qi = lds.q[self];
         const uint32_t cs = lds.cstep[lx + kTileX * (ly + kTileY * lz)];
-        // (none for a particle that is not in its cell, else one or more: i's
-        // own cell is in its stencil)
-        const uint16_t* const p_end = lds.step + (cs & 0xFFFFu) + (cs >> 16) - 1u;
-        const int32_t n_st = qi.y >> 31 ? 0 : (int32_t)(cs >> 16) - 1;
-        const uint16_t* p = p_end - n_st;
+        // (one step or more: i's own cell is in its stencil)
+        const int32_t n_st = (int32_t)(cs >> 16) - 1;
+        const uint16_t* p = lds.step + (cs & 0xFFFFu);
+        const uint16_t* const p_end = p + n_st;
         int32_t left = wave_max(n_st);
         const uint32_t own = (uint32_t)(lx & 3) << 26 | (uint32_t)(ly & 3) << 28 | (uint32_t)(lz & 3) << 30;
         const uint32_t own_lo = own & code_bits & ~hbit, own_hi = ~own & hbit;
@@ -948,8 +954,8 @@ __global__ __launch_bounds__(kW * kWave) void k_nlist_tiles(KParams kp, BatchVie
     }
 }
 
-// Tiles the tile builder left (neighbourhood over the LDS capacity):
-// rest[0] tiles listed in rest[1..], their particles walked by the lane
+// Tiles the tile builder left (neighbourhood over the LDS capacity, or with a
+// particle outside its cell): rest[0] tiles listed in rest[1..], their particles walked by the lane
 // builder.  A lane's walk is one serial chain of some 60 us, and the tiles are
 // few: one wave per workgroup, kRestParts of them to a tile, so that each
 // lane walks one row (256 systems, of which the smallest leave some tiles:
