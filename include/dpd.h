@@ -209,15 +209,15 @@ int dpd_bin_reorder(const dpd_params* p, const dpd_state* in, dpd_state* out,
 /* Ordered neighbour list (Sec. 3.3.2).
  * For a state produced by dpd_bin_reorder (x32 = its FP32 in-cell offsets):
  * row i lists every j != i with |r_ij|^2 < (r_c + skin)^2 (the FP64 rule of
- * the header comment, bit for bit) in strictly ascending j.  One 64-lane
- * wavefront per 2x2x2 block of cells scans the surrounding cells in
- * ascending rank; an FP32 pre-test on the offsets decides all pairs outside
- * a narrow band around the cutoff and the FP64 rule decides inside it;
- * insertion points come from a wavefront ballot and a lane prefix count (no
- * atomics, deterministic).  If the rows need more than nl->capacity entries,
- * DPD_STATUS_NLIST_OVERFLOW is set in *d_status, offset[] still holds the
- * required row sizes (offset[n] = the total needed) and index[] is not
- * written. */
+ * the header comment, bit for bit) in strictly ascending j.  One workgroup
+ * per 8x4x4 tile of cells stages the surrounding cells in LDS, and one lane
+ * per particle walks its 27 cells in ascending rank (dpd_set_list_builder
+ * names the other builders); a test on the offsets, in 16-bit integers or
+ * FP32, decides all pairs outside a narrow band around the cutoff and the
+ * FP64 rule decides inside it (no atomics on rows, deterministic).  If the
+ * rows need more than nl->capacity entries, DPD_STATUS_NLIST_OVERFLOW is set
+ * in *d_status, offset[] still holds the required row sizes (offset[n] = the
+ * total needed) and index[] is not written. */
 int dpd_build_neighbors(const dpd_params* p, const dpd_state* sorted, const dpd_cells* cells,
                         const float* x32, dpd_nlist* nl, int32_t* d_status,
                         void* ws, size_t ws_bytes, void* stream);

@@ -642,8 +642,10 @@ __device__ __forceinline__ bool pair64(const PT& P, const double* A, const doubl
                                        const Op64& oi, const Op64& oj, uint64_t step,
                                        double& px, double& py, double& pz, double& pp)
 {
-    // (the same values as min_image for every pair within r_c, boxes being
-    // 3 r_c wide or more: -L, 0 or L added)
+    // the minimum image as a rounded multiple of L: -L, 0 or L is added in one
+    // rounding, the same values as min_image for every pair within r_c of
+    // positions in the box (boxes are 3 r_c wide or more), in three
+    // instructions a component instead of two compares and their selections
     auto image = [](double d, double L, double inv_L) { return __fma_rn(-__builtin_rint(d * inv_L), L, d); };
     const double dx = image(oi.x - oj.x, P.L[0], P.inv_L[0]);
     const double dy = image(oi.y - oj.y, P.L[1], P.inv_L[1]);

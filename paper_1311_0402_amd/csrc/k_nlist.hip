@@ -1,6 +1,11 @@
 // k_nlist.hip -- ordered neighbour list (Sec. 3.3 of the paper).
 //
-// Work unit: one 64-lane wavefront per Morton-aligned 2x2x2 block of cells.
+// Three builders, with the same rows for positions in the box: by tiles of
+// cells staged in LDS (kind 0, the default; described where it stands), by
+// blocks of cells (kind 1) and by lanes over global memory (kind 2, also the
+// walk of the tiles that the first leaves, and the direct pass).
+//
+// Block builder: one 64-lane wavefront per Morton-aligned 2x2x2 block of cells.
 // The block's cells have consecutive Morton ranks, so its particles (the i
 // side) are one contiguous index range.  The union of their stencils is the
 // 4x4x4 cells around the block (fewer where a side has only 3 cells); lane m
@@ -24,10 +29,9 @@
 // the CSR list.  Rows that do not fit the slab width send the build through
 // a second, direct pass instead (same walk, writing at the scanned offsets).
 //
-// Second work unit (the default while all ranks fit 27 bits): one lane per
-// particle i.  The lane ranks i's 27 stencil cells, sorts them by rank with
-// a fixed comparison network (Batcher's odd-even merge sort), and walks them
-// in that order, each cell's particles in index order, so its row comes out
+// Lane builder (while all ranks fit 27 bits): one lane per particle i.  The
+// lane ranks i's 27 stencil cells, sorts them by rank with a fixed comparison
+// network (Batcher's odd-even merge sort), and walks them in that order, each cell's particles in index order, so its row comes out
 // ascending with no cross-lane work.  Lanes of a wave walk their own k-th
 // stencil cells together; the distance test is the same FP32 pre-test with
 // the same exact FP64 band rule.
@@ -1002,12 +1006,17 @@ void launch_nlist_tiles(int waves, const KParams& kp, const BatchView& bv, int32
                         const int32_t* rank_tab, int32_t* offset, int32_t* slab, int32_t slab_k, int32_t* flag,
                         int32_t* rest, hipStream_t s, Gate gate)
 {
-    // Workgroups sharing a compute unit: as many as its 32 waves allow (8 waves:
-    // four 444 us, three with more words a lane 561 us, for the 256 systems), but
-    // one of 16 waves, with 32 words a lane against 18, where each of the 256
-    // units gets two tiles at most (10 systems of 4,608 particles, 180 tiles:
-    // 46.6 and 54.4 us; 1M particles at r_c + skin, 1,200 tiles: 85 and 84 us,
-    // and 16 us more per build in a long run).
+    // Workgroups sharing a compute unit: as many as its 32 waves allow, but four
+    // of 6 waves (a fifth would leave the runs no room in the words) and one of 16
+    // waves where each of the 256 units gets two tiles at most.  As many, and one
+    // less with more words a lane, on 2M particles: 6 waves (density 2.4) 222 and
+    // 257 us, 7 waves (3) 207 and 221, 10 waves (4.2) 267 and 327, 12 waves (5.2)
+    // 270 and 363; 8 waves, the 256 systems, 444 and 561 us.  On 256 to 500 tiles
+    // the order is the same or within 1.5 us (10 waves, 256 tiles: 35.0 and 33.6;
+    // 12 waves, 405 tiles: 50 and 61).  16 waves, two and one with 32 words a lane
+    // against 18: 10 systems of 4,608 particles, 180 tiles, 54.4 and 46.6 us; 1M
+    // particles at r_c + skin, 1,200 tiles, 85 and 84 us, and 16 us more per build
+    // in a long run with one.
 #define DPD_TILE_CASE(W, G)                                                                                      \
     launch_nlist_tiles_t<kB, W, G>(kp, bv, n_tiles, n, x, x32, cell_xyz, cell_start, rank_tab, offset, slab,      \
                                    slab_k, flag, rest, s, gate)
@@ -1133,8 +1142,7 @@ hipError_t launch_nlist(const KParams& kp, const BatchView& bv, int32_t n_cells,
                            s, n, (const int32_t*)offset, capacity, (const int32_t*)slab, slab_k,
                            (const int32_t*)flag, index);
     // the capacity check, and rows that overflowed the slab: the lane builder's
-    // walk writes the CSR rows directly (the same rows the tile builder would
-    // give)
+    // walk writes the CSR rows directly (the same rows as the tile builder's)
     if (lanes)
         launch_nlist_lanes<true>(waves, kp, bv, n, x, x32, cell_xyz, cell_start, rank_tab, offset, index, capacity,
                                  slab, slab_k, flag, status, s, gate);

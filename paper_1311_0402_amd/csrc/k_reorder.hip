@@ -135,9 +135,9 @@ hipError_t launch_bin(const KParams& kp, const BatchView& bv, int32_t n, const d
 }
 
 // ---------------------------------------------------------------------------
-// Device-wide exclusive scan (three passes: tile sums, scan of the tile
-// sums, tile-local scan plus tile offset).  Tiles of kScanTile items, 256
-// threads x 16 items, wave64 shuffles inside a wave.
+// Device-wide exclusive scan: tile sums, scan of the tile sums, tile-local
+// scan plus tile offset, in one to three launches by size (launch_scan).  Tiles
+// of kScanTile items, 256 threads x 16 items, wave64 shuffles inside a wave.
 // ---------------------------------------------------------------------------
 
 __device__ __forceinline__ int32_t wave_incl_scan(int32_t v)
@@ -287,11 +287,15 @@ hipError_t launch_scan(int32_t* data, int64_t count, int32_t* partials, hipStrea
     if (count <= 0) return hipSuccess;
     const int tiles = ceil_div(count, kScanTile);
     // One tile needs no sums; up to kScanOwn tiles each workgroup adds the sums
-    // before its own, at most 4 KB through the L2; beyond, that would read more
-    // than the third launch costs.  A launch takes 3.5 to 4.5 us: the two scans
-    // of a step 21 -> 7 us for 3,000 particles, 27 -> 18 us for 64,000 (with
-    // the counters cleared by the reorder and the capacity checked by the
-    // direct pass, a step of 3,000 mixed 86 -> 73 us, of 64,000 in FP64 121 -> 114).
+    // before its own, at most 4 KB through the L2, reads that grow with the
+    // square of the tiles.  The last launch of two, and the last two of three
+    // (4.6 us of each the scan of the sums): 245 tiles 5.1 and 9.7 us, 977 8.6
+    // and 11.9, 1,954 11.9 and 13.8, 3,907 23.4 and 25.1.  Two launches are still
+    // ahead there, by 1.7 us of a step of milliseconds; the line keeps the reads
+    // bounded.  The two scans of a step 21 -> 7 us for 3,000 particles, 27 -> 18
+    // us for 64,000 (with the counters cleared by the reorder and the capacity
+    // checked by the direct pass, a step of 3,000 mixed 86 -> 73 us, of 64,000 in
+    // FP64 121 -> 114).
     if (tiles > 1) hipLaunchKernelGGL(k_scan_tiles, dim3(tiles), dim3(kBlock), 0, s, data, count, partials, gate);
     if (tiles <= kScanOwn) {
         hipLaunchKernelGGL(k_scan_apply<true>, dim3(tiles), dim3(kBlock), 0, s, data, count, partials, gate);
