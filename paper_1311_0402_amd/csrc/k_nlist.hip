@@ -455,11 +455,11 @@ void launch_nlist_pass(int waves, const KParams& kp, const BatchView& bv, int32_
 // by side.  Each tile cell's 27 stencil cells are put in ascending rank once,
 // by one lane, with the same sorting network; those that follow each other
 // in LDS as well are joined, which leaves 10.5 runs of slots on average
-// instead of 27; the runs are cut into steps of four candidates, 27 on
+// instead of 27; the runs are cut into steps of four candidates, 25 on
 // average at density 3.  Each lane then walks its particle's steps in that
 // order, so its row comes out ascending.  A step with a hit leaves one 16-bit
 // word in LDS (first slot and four hit bits); the row is written from these
-// words afterwards, 16 bytes per store.
+// words afterwards, two entries per store.
 //
 // Positions are counted in units of 1/13055 of the widest cell, 16 bits per
 // component modulo five cells (a candidate's cell touches the particle's, so
@@ -469,19 +469,22 @@ void launch_nlist_pass(int waves, const KParams& kp, const BatchView& bv, int32_
 // band that their rounding leaves open the FP64 rule decides (0.01 candidates
 // per particle at density 3).
 //
-// What bounds it: instruction issue.  At 16M particles (density 3) a wave
-// takes ~2,700 vector instructions, one per 4.3 clocks and SIMD: the walk 40 %
-// (33 per step of four candidates, 23 of them the distance test),
-// writing the rows 26 %, the sort and the runs 18 %.
-// Hence the wide steps, the joined runs and the integer test; a list of steps
+// What bounds it: no one unit.  At 16M particles (density 3, seven waves per
+// SIMD) a wave takes 2,665 vector instructions (33 per step of four candidates,
+// 23 of them the distance test), one per 4.5 clocks and SIMD, 44 % of the issue
+// peak; the LDS is busy 57 % of the time (21 % in bank conflicts), the address
+// unit 44 %; the rest is waiting for LDS reads, barriers and the longest walk of
+// each wave.  Time followed both the instructions and what is waited for: hence
+// the wide steps, the joined runs and the integer test; a list of steps
 // rather than of runs keeps the walk free of run ends (30 instructions per
 // step fewer); rows leave two entries at a time since scattered stores cost
 // the texture address unit a clock per lane (one at a time 1,482 us at 16M and
 // 57 us at 262,144 particles of density 5, two 1,431 and 47, four 1,448 and
-// 49).  Measured, this kernel before and now: 16M particles 1,660 and 1,430 us;
-// 262,144 in a channel 51 and 46 us; 3,000 25 and 22 us.  Before, candidates
-// were tested in FP32 cell by cell, two per step, 60 steps a row, and each
-// stored or dropped by a scattered store of its own.
+// 49).  Measured, the kernel before it and this one: 16M particles 1,660 and
+// 1,440 us; 262,144 in a channel 51 and 45 us; 3,000 25 and 22 us.  Before,
+// candidates were tested in FP32 cell by cell, two per step, 50 steps a row,
+// and each stored or dropped by a scattered store of its own (2,783
+// instructions a wave).
 //
 // In a grid narrower than the union (fewer than 10 x 6 x 6 cells) a cell can
 // appear in the union at two places, as two periodic images, and is staged
